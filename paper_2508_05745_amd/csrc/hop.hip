@@ -14,29 +14,76 @@
 
 namespace mpsb {
 
-constexpr int HT = 512;
-
-// a double from another lane of the same quad (DPP quad_perm: 0xB1 = lane ^ 1, 0x4E = lane ^ 2)
-template <int CTRL>
-__device__ inline double quad_xor(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 typedef double v4d_t __attribute__((ext_vector_type(4)));
 __device__ inline v4d_t mfma64(double a, double b, v4d_t c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 __device__ inline int pk(int i, int k, int n) { return i * n - (i * (i - 1)) / 2 + (k - i); }   // packed upper
 
-template <typename T, int NMAX>
-__global__ __launch_bounds__(HT) void k_hop_chol(int n, int left_to_right, int other, const c64d* __restrict__ Eg,
+__device__ inline double lane_f64(double x, int l) {   // the value of lane l (uniform) in every lane
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// LDS written by a wave is read by the same wave: no workgroup barrier
+__device__ inline void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// lane L of each row of 16 lanes, in every lane of the row (DPP row_newbcast)
+template <int L>
+__device__ inline double row_bcast(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + L, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + L, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// column JJ of the inverse of a 16 x 16 upper triangle, row ii in the lane's x[], from the
+// columns before it: x[JJ] = -dj sum_l x[l] R[l][JJ], R[l][JJ] still in lane l's x[JJ]
+template <int JJ, int L>
+__device__ inline void inv_sum(const c64d (&x)[16], double (&re)[2], double (&im)[2]) {
+  if constexpr (L < JJ) {
+    const c64d t{row_bcast<L>(x[JJ].re), row_bcast<L>(x[JJ].im)};
+    re[L & 1] = fma(x[L].re, t.re, re[L & 1]);
+    re[L & 1] = fma(-x[L].im, t.im, re[L & 1]);
+    im[L & 1] = fma(x[L].re, t.im, im[L & 1]);
+    im[L & 1] = fma(x[L].im, t.re, im[L & 1]);
+    inv_sum<JJ, L + 1>(x, re, im);
+  }
+}
+template <int JJ>
+__device__ inline void inv_cols(c64d (&x)[16], int ii, const double* ipiv) {
+  if constexpr (JJ < 16) {
+    const double dj = ipiv[JJ];
+    double re[2] = {0, 0}, im[2] = {0, 0};
+    inv_sum<JJ, 0>(x, re, im);
+    if (ii < JJ) x[JJ] = c64d{-dj * (re[0] + re[1]), -dj * (im[0] + im[1])};
+    if (ii == JJ) x[JJ] = c64d{dj, 0.0};
+    inv_cols<JJ + 1>(x, ii, ipiv);
+  }
+}
+
+// What bounds it: chains of dependent steps (pivot, square root, divisions, row updates) at one
+// workgroup per CU for n > 96, where the packed triangle fills the LDS.  A panel of 8 rows of the
+// Cholesky factor is therefore held in the registers of one wave (a lane owns one or two columns,
+// pivots and multipliers by readlane: no barrier and no LDS between its columns) while the other
+// waves apply the previous panel's update to the rows past it; the instances for smaller n leave
+// room for several workgroups per CU.  Every element's operations and their order are those of
+// the column-by-column form (two barriers per column, one instance for all n), bit for bit.
+// Per launch (FP64, 2 n rows), that form -> this one: 1000 trajectories of n = 16 120 -> 28 us,
+// n = 32 222 -> 62; 512 of n = 64 235 -> 122, n = 100 538 -> 431; 1024 of n = 128 1465 -> 1129;
+// 15 of n = 32 58 -> 39, n = 64 118 -> 84, n = 128 334 -> 254.  At n = 128 a workgroup spends a
+// third of that in the product with R^-1 (two thirds of its matrix-core time), a quarter in the
+// panels and a fifth in the inverse's block columns.
+template <typename T, int NMAX, int HT>
+__global__ __launch_bounds__(HT, NMAX > 96 ? 2 : 4) void k_hop_chol(int n, int left_to_right, int other, const c64d* __restrict__ Eg,
                                                  long long sE, cplx<T>* __restrict__ C, long long sC,
                                                  cplx<T>* __restrict__ Rout, long long sR, double tol) {
   __shared__ c64d R[NMAX * (NMAX + 1) / 2];
   __shared__ double piv[NMAX], ipiv[NMAX];   // pivots R[c][c] and their inverses (0 if dropped)
-  __shared__ c64d tcol[NMAX];                 // a column of each diagonal block of R while it is inverted
   __shared__ double red[HT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const c64d* E = Eg + blockIdx.x * sE;
@@ -56,75 +103,111 @@ __global__ __launch_bounds__(HT) void k_hop_chol(int n, int left_to_right, int o
   double dmax = 0;
   for (int w = 0; w < HT / 64; ++w) dmax = fmax(dmax, red[w]);
   const double cut = tol * dmax;
-  // blocked right-looking Cholesky E = R^dag R: panels of CB rows are factored column by
-  // column (updates confined to the panel), then the trailing upper triangle takes the
-  // rank-CB update in 4 x 4 register tiles
-  constexpr int CB = 8;
-  for (int c0 = 0; c0 < n; c0 += CB) {
-    const int cb = min(CB, n - c0);
-    for (int c = c0; c < c0 + cb; ++c) {
-      __syncthreads();   // previous updates complete
-      const double p = R[pk(c, c, n)].re;
+  // blocked right-looking Cholesky E = R^dag R in panels of CB rows: the first wave factors the
+  // rows c0 .. c0+cb-1 (updated by every earlier panel) in registers, lane l owning columns l
+  // and l + 64
+  constexpr int CB = 8, KS = (NMAX + 63) / 64;
+  auto factor = [&](int c0) {
+    c64d v[CB][KS];   // rows past n are zero: no pivot
+#pragma unroll
+    for (int a = 0; a < CB; ++a)
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const int i = c0 + a, k = lane + 64 * s;
+        v[a][s] = (k >= i && k < n) ? R[pk(i, k, n)] : c64d{0, 0};
+      }
+    const int l0 = c0 & 63;
+    const bool up = KS > 1 && c0 >= 64;    // the panel's own columns are in the second set
+#pragma unroll
+    for (int a = 0; a < CB; ++a) {
+      const c64d own = up ? v[a][KS - 1] : v[a][0];
+      const double p = lane_f64(own.re, l0 + a);
       const bool keep = p > cut && p > 0.0;
       const double r = keep ? sqrt(p) : 0.0;
-      // row c past the diagonal; the pivot itself is overwritten after the next barrier, once
-      // every thread has read it (nothing below reads it)
-      for (int k = c + 1 + tid; k < n; k += HT) {
-        c64d v = R[pk(c, k, n)];
-        R[pk(c, k, n)] = keep ? c64d{v.re / r, v.im / r} : c64d{0, 0};
+      if (lane == 0) piv[c0 + a] = r;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const c64d x = v[a][s];
+        v[a][s] = keep ? c64d{x.re / r, x.im / r} : c64d{0, 0};
       }
-      if (tid == 0) {
-        piv[c] = r;
-        ipiv[c] = keep ? 1.0 / r : 0.0;
+      // rows c+1 .. of the panel: E[i][k] -= conj(R[c][i]) R[c][k] (nothing for a dropped pivot,
+      // whose row is zero)
+      const c64d row = up ? v[a][KS - 1] : v[a][0];
+#pragma unroll
+      for (int b = a + 1; b < CB; ++b) {
+        const c64d f{lane_f64(row.re, l0 + b), lane_f64(row.im, l0 + b)};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) v[b][s] = v[b][s] - cmulc(f, v[a][s]);
       }
-      __syncthreads();
-      if (tid == 0) R[pk(c, c, n)] = c64d{r, 0.0};
-      // rows c+1 .. c0+cb-1 of the panel, a wave per row: E[i][k] -= conj(R[c][i]) R[c][k], k >= i
-      if (keep) {
-        for (int i = c + 1 + wv; i < c0 + cb; i += HT / 64)
-          for (int k = i + lane; k < n; k += 64) R[pk(i, k, n)] = R[pk(i, k, n)] - cmulc(R[pk(c, i, n)], R[pk(c, k, n)]);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const int i = c0 + a, k = lane + 64 * s;
+        if (k >= i && k < n) R[pk(i, k, n)] = k == i ? c64d{r, 0.0} : v[a][s];
       }
     }
+  };
+  if (wv == 0) factor(0);
+  __syncthreads();
+  for (int c0 = 0; c0 + CB < n; c0 += CB) {
+    // the panel's update of the rows t0 .. n-1: first the rows of the next panel by every
+    // wave, a row at a time, then the rest in 4 x 4 register tiles while the first wave
+    // factors that panel
+    const int t0 = c0 + CB;
+    for (int i = t0 + wv; i < min(t0 + CB, n); i += HT / 64)
+      for (int k = i + lane; k < n; k += 64) {
+        c64d acc{0, 0};
+#pragma unroll
+        for (int cc = 0; cc < CB; ++cc) {
+          const int c = c0 + cc;
+          const c64d* row = R + (pk(c, c, n) - c);   // row[k] = R[c][k], zero for a dropped pivot
+          acc = acc + cmulc(row[i], row[k]);
+        }
+        R[pk(i, k, n)] = R[pk(i, k, n)] - acc;
+      }
     __syncthreads();
-    // trailing update, rows and columns >= t0 = c0 + cb, upper triangle in 4 x 4 tiles
-    const int t0 = c0 + cb, m = n - t0;
-    if (m <= 0) continue;
-    const int nt = (m + 3) / 4, ntiles = nt * (nt + 1) / 2;
-    for (int t = tid; t < ntiles; t += HT) {
-      // tile (ti, tk), tk >= ti, linear index t = tk (tk + 1) / 2 + ti
-      int tk = (int)((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
-      while (tk * (tk + 1) / 2 > t) --tk;
-      while ((tk + 1) * (tk + 2) / 2 <= t) ++tk;
-      const int ti = t - tk * (tk + 1) / 2;
-      const int i0 = t0 + 4 * ti, k0 = t0 + 4 * tk;
-      c64d acc[4][4];
+    if (wv == 0) {
+      factor(t0);
+    } else {
+      const int t1 = t0 + CB, m = max(0, n - t1);
+      const int nt = (m + 3) / 4, ntiles = nt * (nt + 1) / 2;
+      for (int t = tid - 64; t < ntiles; t += HT - 64) {
+        // tile (ti, tk), tk >= ti, linear index t = tk (tk + 1) / 2 + ti
+        int tk = (int)((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
+        while (tk * (tk + 1) / 2 > t) --tk;
+        while ((tk + 1) * (tk + 2) / 2 <= t) ++tk;
+        const int ti = t - tk * (tk + 1) / 2;
+        const int i0 = t1 + 4 * ti, k0 = t1 + 4 * tk;
+        c64d acc[4][4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = c64d{0, 0};
-      for (int c = c0; c < t0; ++c) {
-        if (!(piv[c] > 0.0)) continue;
-        c64d ri[4], rk[4];
+          for (int b = 0; b < 4; ++b) acc[a][b] = c64d{0, 0};
+#pragma unroll 2
+        for (int c = c0; c < t0; ++c) {
+          c64d ri[4], rk[4];
+          const c64d* row = R + (pk(c, c, n) - c);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          ri[a] = (i0 + a < n) ? R[pk(c, i0 + a, n)] : c64d{0, 0};
-          rk[a] = (k0 + a < n) ? R[pk(c, k0 + a, n)] : c64d{0, 0};
+          for (int a = 0; a < 4; ++a) {   // past n: read but not used (min: inside the triangle)
+            ri[a] = row[min(i0 + a, n - 1)];
+            rk[a] = row[min(k0 + a, n - 1)];
+          }
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = acc[a][b] + cmulc(ri[a], rk[b]);
         }
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
-          for (int b = 0; b < 4; ++b) acc[a][b] = acc[a][b] + cmulc(ri[a], rk[b]);
+          for (int b = 0; b < 4; ++b) {
+            const int i = i0 + a, k = k0 + b;
+            if (i < n && k < n && k >= i) R[pk(i, k, n)] = R[pk(i, k, n)] - acc[a][b];
+          }
       }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int i = i0 + a, k = k0 + b;
-          if (i < n && k < n && k >= i) R[pk(i, k, n)] = R[pk(i, k, n)] - acc[a][b];
-        }
     }
+    __syncthreads();
   }
-  __syncthreads();
+  if (tid < n) ipiv[tid] = piv[tid] > 0.0 ? 1.0 / piv[tid] : 0.0;
   // R out (upper, zeros below), precision of the state
   for (int i = wv; i < n; i += HT / 64)
     for (int k = lane; k < n; k += 64) {
@@ -140,119 +223,97 @@ __global__ __launch_bounds__(HT) void k_hop_chol(int n, int left_to_right, int o
   // the substitution would.
   __syncthreads();   // R has been written out
   const int nbk = (n + 15) / 16;
-  static_assert(HT >= 16 * (NMAX / 16), "a thread per row of every diagonal block");
-  {
-    const int b = tid >> 4, ii = tid & 15, r0 = 16 * b;
+  const int i16 = lane & 15, kq = lane >> 4;
+  constexpr int NT16 = NMAX / 16;
+  static_assert(HT >= NMAX && HT / 64 >= NT16 - 1, "a thread per row of a diagonal block, a wave per row block");
+  if (tid < NMAX) {
+    // diagonal blocks: row ii of block b in the registers of thread 16 b + ii, the column of R
+    // from the other rows' threads by DPP row broadcasts.  Zeros stand for the elements left of
+    // the diagonal; the even and the odd terms are summed apart.
+    const int b = tid >> 4, ii = i16, r0 = 16 * b;
     const int bs = b < nbk ? min(16, n - r0) : 0;
-    for (int jj = 0; jj < 16; ++jj) {
-      if (ii < jj && jj < bs) tcol[r0 + ii] = R[pk(r0 + ii, r0 + jj, n)];
-      __syncthreads();
-      if (jj < bs) {
-        const int i = r0 + ii, j = r0 + jj;
-        const double dj = ipiv[j];
-        if (ii < jj) {
-          double yr0 = 0.0, yi0 = 0.0, yr1 = 0.0, yi1 = 0.0;
-          int l = ii;
-          for (; l + 1 < jj; l += 2) {
-            const c64d a0 = R[pk(i, r0 + l, n)], x0 = tcol[r0 + l], a1 = R[pk(i, r0 + l + 1, n)], x1 = tcol[r0 + l + 1];
-            yr0 = fma(a0.re, x0.re, yr0);
-            yr0 = fma(-a0.im, x0.im, yr0);
-            yi0 = fma(a0.re, x0.im, yi0);
-            yi0 = fma(a0.im, x0.re, yi0);
-            yr1 = fma(a1.re, x1.re, yr1);
-            yr1 = fma(-a1.im, x1.im, yr1);
-            yi1 = fma(a1.re, x1.im, yi1);
-            yi1 = fma(a1.im, x1.re, yi1);
-          }
-          if (l < jj) {
-            const c64d a0 = R[pk(i, r0 + l, n)], x0 = tcol[r0 + l];
-            yr0 = fma(a0.re, x0.re, yr0);
-            yr0 = fma(-a0.im, x0.im, yr0);
-            yi0 = fma(a0.re, x0.im, yi0);
-            yi0 = fma(a0.im, x0.re, yi0);
-          }
-          R[pk(i, j, n)] = c64d{-dj * (yr0 + yr1), -dj * (yi0 + yi1)};
-        } else if (ii == jj) {
-          R[pk(j, j, n)] = c64d{dj, 0.0};
-        }
-      }
-      __syncthreads();
-    }
+    c64d x[16];
+#pragma unroll
+    for (int l = 0; l < 16; ++l) x[l] = (l >= ii && l < bs) ? R[pk(r0 + ii, r0 + l, n)] : c64d{0, 0};
+    inv_cols<0>(x, ii, ipiv + min(r0, NMAX - 16));
+#pragma unroll
+    for (int l = 0; l < 16; ++l)
+      if (l >= ii && l < bs) R[pk(r0 + ii, r0 + l, n)] = x[l];
   }
-  // block columns J >= 1: element (i, jj) of the a x 16 block above the diagonal in thread
-  // (16 i + jj) mod HT, at most four per thread (a <= NMAX - 16)
-  constexpr int PER = ((NMAX - 16) * 16 + HT - 1) / HT;
+  __syncthreads();
+  // block columns J >= 1, rows 16 I .. of the block above the diagonal by wave I.  The chains of
+  // four fmas that the f64 MFMA runs along K are those of a sum over l taken term by term (real
+  // part: x.re r.re, then -x.im r.im), two rows l of the same parity per instruction.
   for (int J = 1; J < nbk; ++J) {
-    const int a = 16 * J, cw = min(16, n - a);
-    c64d yv[PER];
+    const int a = 16 * J, cw = min(16, n - a), I = wv, cl = a + min(i16, cw - 1);
+    v4d_t y[2][2];                       // [parity of l][re, im]
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + HT * q, i = e >> 4, jj = e & 15;
-      double yr0 = 0.0, yi0 = 0.0, yr1 = 0.0, yi1 = 0.0;
-      if (i < a && jj < cw) {
-        // Y[i][jj] = sum_{l = i}^{a-1} X[i][l] R[l][a + jj]
-        const int base = pk(i, i, n) - i;   // X[i][l] = R[base + l], l >= i
-        int l = i;
-        for (; l + 1 < a; l += 2) {
-          const c64d x0 = R[base + l], r0v = R[pk(l, a + jj, n)], x1 = R[base + l + 1], r1v = R[pk(l + 1, a + jj, n)];
-          yr0 = fma(x0.re, r0v.re, yr0);
-          yr0 = fma(-x0.im, r0v.im, yr0);
-          yi0 = fma(x0.re, r0v.im, yi0);
-          yi0 = fma(x0.im, r0v.re, yi0);
-          yr1 = fma(x1.re, r1v.re, yr1);
-          yr1 = fma(-x1.im, r1v.im, yr1);
-          yi1 = fma(x1.re, r1v.im, yi1);
-          yi1 = fma(x1.im, r1v.re, yi1);
+    for (int z = 0; z < 2; ++z) y[z][0] = y[z][1] = v4d_t{0, 0, 0, 0};
+    const bool odd = kq & 1;
+    if (I < J) {
+      // Y[i][jj] = sum_{l >= i} X[i][l] R[l][a + jj], the operands loaded a step ahead
+      const int i = 16 * I + i16;
+      const c64d* xrow = R + (pk(i, i, n) - i);
+      c64d xv[2], rv[2];
+      auto load = [&](int l0) {
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {   // (l < i: some other element of the triangle, not used)
+          const int l = min(l0, a - 4) + z + (kq & 2);
+          xv[z] = xrow[l];
+          rv[z] = R[pk(l, cl, n)];
+          if (l < i) xv[z] = c64d{0, 0};
         }
-        if (l < a) {
-          const c64d x0 = R[base + l], r0v = R[pk(l, a + jj, n)];
-          yr0 = fma(x0.re, r0v.re, yr0);
-          yr0 = fma(-x0.im, r0v.im, yr0);
-          yi0 = fma(x0.re, r0v.im, yi0);
-          yi0 = fma(x0.im, r0v.re, yi0);
+      };
+      load(16 * I);
+      for (int l0 = 16 * I; l0 < a; l0 += 4) {
+        double p[2][2], r[2][2];
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          p[z][0] = odd ? -xv[z].im : xv[z].re;
+          r[z][0] = odd ? rv[z].im : rv[z].re;
+          p[z][1] = odd ? xv[z].im : xv[z].re;
+          r[z][1] = odd ? rv[z].re : rv[z].im;
         }
-      }
-      yv[q] = c64d{yr0 + yr1, yi0 + yi1};
-    }
-    __syncthreads();   // block column J of R has been read
+        load(l0 + 4);
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + HT * q, i = e >> 4, jj = e & 15;
-      if (i < a && jj < cw) R[pk(i, a + jj, n)] = yv[q];
-    }
-    __syncthreads();
-    // X[i][a + jj] = -sum_{m <= jj} Y[i][m] X_JJ[m][jj]
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + HT * q, i = e >> 4, jj = e & 15;
-      double xr = 0.0, xi = 0.0;
-      if (i < a && jj < cw) {
-        for (int m = 0; m <= jj; ++m) {
-          const c64d y = R[pk(i, a + m, n)], z = R[pk(a + m, a + jj, n)];
-          xr = fma(y.re, z.re, xr);
-          xr = fma(-y.im, z.im, xr);
-          xi = fma(y.re, z.im, xi);
-          xi = fma(y.im, z.re, xi);
+        for (int z = 0; z < 2; ++z) {
+          y[z][0] = mfma64(p[z][0], r[z][0], y[z][0]);
+          y[z][1] = mfma64(p[z][1], r[z][1], y[z][1]);
         }
       }
-      yv[q] = c64d{-xr, -xi};
     }
-    __syncthreads();   // Y has been read
+    __syncthreads();                     // block column J of R has been read
+    if (I < J) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + HT * q, i = e >> 4, jj = e & 15;
-      if (i < a && jj < cw) R[pk(i, a + jj, n)] = yv[q];
+      for (int q = 0; q < 4; ++q)
+        if (i16 < cw) R[pk(16 * I + 4 * q + kq, a + i16, n)] = c64d{y[0][0][q] + y[1][0][q], y[0][1][q] + y[1][1][q]};
+      wave_fence();
+      // X[i][a + jj] = -sum_{m <= jj} Y[i][m] X_JJ[m][jj]
+      v4d_t xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0};
+#pragma unroll
+      for (int m0 = 0; m0 < 16; m0 += 2) {
+        const int m = m0 + (kq >> 1);
+        const int mc = min(m, cw - 1);
+        c64d yv = R[pk(16 * I + i16, a + mc, n)], zv = R[pk(a + mc, cl, n)];
+        if (m >= cw) yv = c64d{0, 0};
+        if (m > i16) zv = c64d{0, 0};
+        xr = mfma64(odd ? -yv.im : yv.re, odd ? zv.im : zv.re, xr);
+        xi = mfma64(odd ? yv.im : yv.re, odd ? zv.re : zv.im, xi);
+      }
+      wave_fence();
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i16 < cw) R[pk(16 * I + 4 * q + kq, a + i16, n)] = c64d{-xr[q], -xi[q]};
+      wave_fence();                      // read by this wave alone until the last barrier
     }
-    __syncthreads();
   }
+  __syncthreads();
   // Q = C R^{-1} (L->R, C: other x n, row-major) or Q = R^{-dag} C (R->L, C: n x other), in
   // place, on f64 MFMA over the nonzero triangle of R^{-1}.  A wave owns 16 rows (L->R) or
   // 16 columns (R->L) of C with all their output tiles in registers, so it reads those rows /
   // columns completely before it writes them.  Lane layout (f64 16x16x4): A[i][k] in lane
   // i + 16 k, B[k][j] in lane j + 16 k, D[i][j] in lane j + 16 (i % 4), register i / 4.
-  const int i16 = lane & 15, kq = lane >> 4;
-  constexpr int NT16 = NMAX / 16;
-  const int nt = (n + 15) / 16;
+  const int nt = nbk;
   if (left_to_right) {
     const int nvt = (other + 15) / 16;
     for (int vt = wv; vt < nvt; vt += HT / 64) {
@@ -260,22 +321,32 @@ __global__ __launch_bounds__(HT) void k_hop_chol(int n, int left_to_right, int o
 #pragma unroll
       for (int t = 0; t < NT16; ++t) ar[t] = ai[t] = v4d_t{0, 0, 0, 0};
       const int v = 16 * vt + i16;
+      // the step's operands are loaded before its products, the row of C a step ahead
+      auto row = [&](int l) { return v < other && l < n ? Cj[(long long)v * n + l] : cplx<T>{0, 0}; };
+      cplx<T> cn = row(kq);
       for (int l0 = 0; l0 < n; l0 += 4) {
         const int l = l0 + kq;
-        cplx<T> cv = {0, 0};
-        if (v < other && l < n) cv = Cj[(long long)v * n + l];
+        const cplx<T> cv = cn;
+        cn = row(l + 4);
         const double cr = (double)cv.re, ci = (double)cv.im;
+        c64d b[NT16];
+        const c64d* rl = R + pk(min(l, n - 1), 0, n);   // rl[c] = Rinv[l][c]
 #pragma unroll
-        for (int t = 0; t < NT16; ++t) {
+        for (int t = 0; t < NT16; ++t)
           if (t < nt && l0 <= 16 * t + 15) {   // Rinv[l][c] = 0 for l > c
             const int c = 16 * t + i16;
-            const c64d b = (l < n && c < n && l <= c) ? R[pk(l, c, n)] : c64d{0, 0};
-            ar[t] = mfma64(cr, b.re, ar[t]);
-            ar[t] = mfma64(-ci, b.im, ar[t]);
-            ai[t] = mfma64(cr, b.im, ai[t]);
-            ai[t] = mfma64(ci, b.re, ai[t]);
+            b[t] = rl[min(c, n - 1)];          // (l > c: some other element, not used)
+            if (t == (l0 >> 4) || t == nt - 1)
+              if (!(l < n && c < n && l <= c)) b[t] = c64d{0, 0};
           }
-        }
+#pragma unroll
+        for (int t = 0; t < NT16; ++t)
+          if (t < nt && l0 <= 16 * t + 15) {
+            ar[t] = mfma64(cr, b[t].re, ar[t]);
+            ai[t] = mfma64(cr, b[t].im, ai[t]);
+            ar[t] = mfma64(-ci, b[t].im, ar[t]);
+            ai[t] = mfma64(ci, b[t].re, ai[t]);
+          }
       }
 #pragma unroll
       for (int t = 0; t < NT16; ++t)
@@ -292,23 +363,32 @@ __global__ __launch_bounds__(HT) void k_hop_chol(int n, int left_to_right, int o
 #pragma unroll
       for (int t = 0; t < NT16; ++t) ar[t] = ai[t] = v4d_t{0, 0, 0, 0};
       const int v = 16 * vt + i16;
+      auto col = [&](int l) { return v < other && l < n ? Cj[(long long)l * other + v] : cplx<T>{0, 0}; };
+      cplx<T> cn = col(kq);
       for (int l0 = 0; l0 < n; l0 += 4) {
         const int l = l0 + kq;
-        cplx<T> cv = {0, 0};
-        if (v < other && l < n) cv = Cj[(long long)l * other + v];
+        const cplx<T> cv = cn;
+        cn = col(l + 4);
         const double br = (double)cv.re, bi = (double)cv.im;
+        c64d a[NT16];
+        const c64d* rl = R + pk(min(l, n - 1), 0, n);
 #pragma unroll
-        for (int t = 0; t < NT16; ++t) {
+        for (int t = 0; t < NT16; ++t)
           if (t < nt && l0 <= 16 * t + 15) {   // conj(Rinv[l][r]) = 0 for l > r
             const int r = 16 * t + i16;
-            const c64d a = (l < n && r < n && l <= r) ? R[pk(l, r, n)] : c64d{0, 0};
-            // A[r][l] = conj(Rinv[l][r])
-            ar[t] = mfma64(a.re, br, ar[t]);
-            ar[t] = mfma64(a.im, bi, ar[t]);
-            ai[t] = mfma64(a.re, bi, ai[t]);
-            ai[t] = mfma64(-a.im, br, ai[t]);
+            a[t] = rl[min(r, n - 1)];
+            if (t == (l0 >> 4) || t == nt - 1)
+              if (!(l < n && r < n && l <= r)) a[t] = c64d{0, 0};
           }
-        }
+        // A[r][l] = conj(Rinv[l][r])
+#pragma unroll
+        for (int t = 0; t < NT16; ++t)
+          if (t < nt && l0 <= 16 * t + 15) {
+            ar[t] = mfma64(a[t].re, br, ar[t]);
+            ai[t] = mfma64(a[t].re, bi, ai[t]);
+            ar[t] = mfma64(a[t].im, bi, ar[t]);
+            ai[t] = mfma64(-a[t].im, br, ai[t]);
+          }
       }
 #pragma unroll
       for (int t = 0; t < NT16; ++t)
@@ -321,15 +401,30 @@ __global__ __launch_bounds__(HT) void k_hop_chol(int n, int left_to_right, int o
   }
 }
 
+namespace {
+template <typename T, int NMAX, int HT>
+void launch_chol(int n, int left_to_right, int other, const void* E, long long sE, void* C, long long sC, void* Rout,
+                 long long sR, double tol, int n_traj, hipStream_t st) {
+  hipLaunchKernelGGL((k_hop_chol<T, NMAX, HT>), dim3(n_traj), dim3(HT), 0, st, n, left_to_right, other, (const c64d*)E, sE,
+                     (cplx<T>*)C, sC, (cplx<T>*)Rout, sR, tol);
+}
+template <typename T>
+void launch_chol_n(int n, int left_to_right, int other, const void* E, long long sE, void* C, long long sC, void* Rout,
+                   long long sR, double tol, int n_traj, hipStream_t st) {
+  // the smallest triangle that holds the factor: 9, 35 and 78 KB of LDS leave room for several
+  // workgroups per CU, the 136 KB of the last for one (at n <= 64 with that one: 222, 235 us)
+  if (n <= 32) launch_chol<T, 32, 256>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
+  else if (n <= 64) launch_chol<T, 64, 256>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
+  else if (n <= 96) launch_chol<T, 96, 512>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
+  else launch_chol<T, 128, 512>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
+}
+}  // namespace
+
 hipError_t hop_chol(int prec, int n, int left_to_right, int other, const void* E, long long sE, void* C, long long sC,
                     void* Rout, long long sR, double tol, int n_traj, hipStream_t st) {
   if (n > 128) return hipErrorInvalidValue;
-  if (prec == 0)
-    hipLaunchKernelGGL((k_hop_chol<float, 128>), dim3(n_traj), dim3(HT), 0, st, n, left_to_right, other,
-                       (const c64d*)E, sE, (c32*)C, sC, (c32*)Rout, sR, tol);
-  else
-    hipLaunchKernelGGL((k_hop_chol<double, 128>), dim3(n_traj), dim3(HT), 0, st, n, left_to_right, other,
-                       (const c64d*)E, sE, (c64d*)C, sC, (c64d*)Rout, sR, tol);
+  if (prec == 0) launch_chol_n<float>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
+  else launch_chol_n<double>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
   return hipGetLastError();
 }
 

@@ -1,0 +1,33 @@
+"""Truncating chains at the bond dimensions where the splits and the centre hops change kernel
+instance (factors of 32, 64, 96 and 128 rows, Gram matrices of twice that), fill it exactly, or
+leave one row over; against the oracle's SVD truncation.
+
+Phase noise in the state-independent unravelling draws the same branches on both sides, so the
+per-trajectory observables and discarded weights compare directly, at the 1e-10 of all FP64
+trajectories."""
+import numpy as np
+import pytest
+
+from paper_2508_05745_amd import inputs as I
+
+from gpu_util import oracle_obs_mps, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("chi,n,depth", [(3, 6, 6), (8, 9, 7), (9, 9, 7), (15, 10, 8), (16, 10, 8), (17, 11, 8), (31, 12, 8),
+                                         (32, 12, 8), (33, 13, 9), (63, 14, 9), (64, 14, 9), (65, 15, 10), (96, 15, 10), (97, 15, 10),
+                                         (127, 16, 10), (128, 16, 10)])
+def test_truncation_at_instance_edges(chi, n, depth):
+    from paper_2508_05745_amd import mpsb as M
+    c = I.brickwork(n, depth, seed=700 + chi, channel=I.dephasing(0.1))
+    n_traj = 3 if chi <= 33 else 1
+    out = run_gpu(c, chi, n_traj, 91, M.FP64, M.ORTHOGONAL, record=True)
+    truncated = 0
+    for t in range(n_traj):
+        ref, eps = oracle_obs_mps(c, chi, t, 91, M.ORTHOGONAL)
+        disc = np.concatenate([out["disc"][l][t, : len(c.pairs(l))][:: 1 if l % 2 == 0 else -1] for l in range(depth)])
+        assert np.abs(out["per_traj"][t] - ref).max() < 1e-10
+        assert np.abs(disc - np.array(eps)).max() < 1e-10
+        truncated += int((np.array(eps) > 1e-9).sum())
+    assert truncated > 0

@@ -25,6 +25,7 @@ namespace mpsb {
 
 constexpr int ET = 256;           // threads per workgroup
 constexpr int EMAX = 512;         // largest matrix dimension
+constexpr int TRI_LDS_MAX = 2048; // n keep up to which the inverse iteration runs in LDS
 
 // Cross-lane moves of doubles on the VALU, without the LDS crossbar: DPP within rows of 16
 // lanes (quad_perm 0xB1 = lane ^ 1, 0x4E = lane ^ 2, row_half_mirror 0x141 = 7 - lane within
@@ -495,8 +496,8 @@ __global__ __launch_bounds__(NT, WPE) void k_tridiag(int n, c64d* __restrict__ A
 }
 
 // ---------------------------------------------------------------------------- E2
-// Sturm counts: numbers of eigenvalues of the real symmetric tridiagonal (d, e) below x1 and
-// below x2, from the pivots of the LDL^T factorisations of T - x (two independent chains
+// Sturm counts: numbers of eigenvalues of the real symmetric tridiagonal (d, e) below the C
+// points x, from the pivots of the LDL^T factorisations of T - x (independent chains
 // interleaved).  1/q is the hardware reciprocal refined by one Newton step (relative error
 // below 2^-50, a perturbation of e^2 of that order); pivots below pivmin are replaced by
 // -pivmin.
@@ -505,26 +506,75 @@ __device__ inline double recip(double q) {
   return fma(r, fma(-q, r, 1.0), r);
 }
 
-__device__ inline void sturm_count2(int n, const double* d, const double* e2, double x1, double x2, double pivmin,
-                                    int& c1, int& c2) {
-  int n1 = 0, n2 = 0;
-  double q1 = d[0] - x1, q2 = d[0] - x2;
-  if (fabs(q1) < pivmin) q1 = -pivmin;
-  if (fabs(q2) < pivmin) q2 = -pivmin;
-  n1 += q1 < 0;
-  n2 += q2 < 0;
-#pragma unroll 4
+template <int C>
+__device__ inline void sturm_guarded(int n, const double* d, const double* e2, const double (&x)[C], double pivmin,
+                                     int (&c)[C]) {
+  double q[C];
+#pragma unroll
+  for (int h = 0; h < C; ++h) {
+    q[h] = d[0] - x[h];
+    if (fabs(q[h]) < pivmin) q[h] = -pivmin;
+    c[h] = q[h] < 0;
+  }
   for (int i = 1; i < n; ++i) {
     const double di = d[i], ei = e2[i - 1];
-    q1 = fma(-ei, recip(q1), di - x1);
-    q2 = fma(-ei, recip(q2), di - x2);
-    if (fabs(q1) < pivmin) q1 = -pivmin;
-    if (fabs(q2) < pivmin) q2 = -pivmin;
-    n1 += q1 < 0;
-    n2 += q2 < 0;
+#pragma unroll
+    for (int h = 0; h < C; ++h) {
+      q[h] = fma(-ei, recip(q[h]), di - x[h]);
+      if (fabs(q[h]) < pivmin) q[h] = -pivmin;
+      c[h] += q[h] < 0;
+    }
   }
-  c1 = n1;
-  c2 = n2;
+}
+
+// The chain is issue-bound (10 instructions per pivot with the comparison, the replacement and
+// the count): the smallest |pivot| is kept instead, the signs are shifted into a word, and the
+// guarded form runs only when some pivot was below pivmin.
+template <int C>
+__device__ inline void sturm_count(int n, const double* d, const double* e2, const double (&x)[C], double pivmin,
+                                   int (&c)[C]) {
+  double q[C], mn[C];
+  unsigned sg[C];
+  auto sign_in = [](unsigned s, double v) {
+    return __builtin_amdgcn_alignbit(s, (unsigned)(__double_as_longlong(v) >> 32), 31);   // (s << 1) | sign
+  };
+#pragma unroll
+  for (int h = 0; h < C; ++h) {
+    q[h] = d[0] - x[h];
+    mn[h] = fabs(q[h]);
+    sg[h] = sign_in(0, q[h]);
+    c[h] = 0;
+  }
+  for (int i0 = 1; i0 < n; i0 += 16) {
+    auto step = [&](int i) {
+      const double di = d[i], ei = e2[i - 1];
+#pragma unroll
+      for (int h = 0; h < C; ++h) {
+        q[h] = fma(-ei, recip(q[h]), di - x[h]);
+        mn[h] = fmin(mn[h], fabs(q[h]));
+        sg[h] = sign_in(sg[h], q[h]);
+      }
+    };
+    if (i0 + 16 <= n) {
+#pragma unroll
+      for (int z = 0; z < 16; ++z) step(i0 + z);
+    } else {
+      for (int i = i0; i < n; ++i) step(i);
+    }
+#pragma unroll
+    for (int h = 0; h < C; ++h) {
+      c[h] += __popc(sg[h]);
+      sg[h] = 0;
+    }
+  }
+  if (n == 1) {
+#pragma unroll
+    for (int h = 0; h < C; ++h) c[h] = (int)sg[h];
+  }
+  bool low = false;
+#pragma unroll
+  for (int h = 0; h < C; ++h) low |= !(mn[h] >= pivmin);
+  if (low) sturm_guarded<C>(n, d, e2, x, pivmin, c);
 }
 
 __device__ inline uint32_t hash32(uint32_t x) {
@@ -532,26 +582,38 @@ __device__ inline uint32_t hash32(uint32_t x) {
   return x;
 }
 
-__global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol, double* __restrict__ ws, long long sW,
+// One thread per eigenvalue alone makes both halves chains that most of a workgroup waits for.
+// Bisection: G lanes per eigenvalue evaluate the brackets of the next 3, 2 or 1 trisection steps
+// at once (16 lanes, the two points of a bracket each, for keep <= 16; 8, a point each, for
+// keep <= 32; 4 for keep <= 64; one past that, where the lanes are busy: eight points per
+// eigenvalue took 5.4 instead of 5.2 ms per 2048 n = 256 matrices); the brackets, their points
+// and the steps taken are those of one step at a time, so the eigenvalues are the same bits.
+// Inverse iteration: the factors and the vector of n keep <= TRI_LDS_MAX elements stay in LDS
+// (LDSF), larger ones are loaded CH steps at a time, one memory latency per CH steps of a solve's
+// chain (8 for keep > 64, whose occupancy 16 costs: 1024 n = 256 matrices 2.32 against 3.10 ms).
+// Per launch, one lane per eigenvalue with factors in memory 4 steps at a time -> this: 15
+// matrices of n = 32 143 -> 65 us, n = 64 260 -> 107, n = 128 421 -> 248; 500 of n = 100 541 ->
+// 424, 512 of n = 128 514 -> 376, 1024 of n = 256 2.57 -> 2.32 ms.  What is left is the chain of
+// the Sturm counts (55% at n = 64), then the factorisation's divisions.
+template <bool LDSF, int CH>
+__global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, int G, double zero_tol, double* __restrict__ ws, long long sW,
                                                 double* __restrict__ evals, long long sE, double* __restrict__ kept_sum,
                                                 const int* __restrict__ active) {
   if (active && !active[blockIdx.x]) return;
+  extern __shared__ double dyn[];   // LDSF: X, U0, U1, U2, L, PV [n][keep]
   __shared__ double sd[EMAX], se[EMAX], se2[EMAX];
   __shared__ c64d sph[EMAX];   // phases of the subdiagonal
+  __shared__ double sev[EMAX / 2];   // the kept eigenvalues
   __shared__ double red[ET / 64];
-  __shared__ double s_bounds[3];
+  __shared__ double s_b[4][ET / 64];
   double* W = ws + blockIdx.x * sW;
   double* d = W;
   c64d* ec = (c64d*)(W + n);
   c64d* om = (c64d*)(W + 4 * n);            // [n] phases omega
-  double* X = W + 6 * n;                    // [n][keep]   vectors (component-major)
-  double* U0 = X + (long long)n * keep;     // [n][keep]   LU factors
-  double* U1 = U0 + (long long)n * keep;
-  double* U2 = U1 + (long long)n * keep;
-  double* L = U2 + (long long)n * keep;
-  double* PV = L + (long long)n * keep;
+  double* Xg = W + 6 * n;                   // [n][keep]   vectors (component-major)
+  const long long nk = (long long)n * keep;
   double* ev = evals + blockIdx.x * sE;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 
   for (int i = tid; i < n; i += ET) {
     sd[i] = d[i];
@@ -562,38 +624,39 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
     sph[i] = a > 0 ? c64d{e.re / a, e.im / a} : c64d{1.0, 0.0};
   }
   __syncthreads();
-  if (tid == 0) {
-    c64d w = {1.0, 0.0};
-    om[0] = w;
-#pragma unroll 8
-    for (int i = 0; i + 1 < n; ++i) {
-      if (se[i] > 0) w = w * sph[i];
-      om[i + 1] = w;
-    }
-    double lo = 1e300, hi = -1e300, emax2 = 0;
-    for (int i = 0; i < n; ++i) {
-      double r = (i > 0 ? se[i - 1] : 0.0) + (i + 1 < n ? se[i] : 0.0);
-      lo = fmin(lo, sd[i] - r);
-      hi = fmax(hi, sd[i] + r);
-      if (i + 1 < n) emax2 = fmax(emax2, se2[i]);
-    }
-    double nrm = fmax(fabs(lo), fabs(hi));
-    lo -= 2 * DBL_EPSILON * nrm + 1e-300;
-    hi += 2 * DBL_EPSILON * nrm + 1e-300;
-    s_bounds[0] = lo;
-    s_bounds[1] = hi;
-    double dmax = 0;
-    for (int i = 0; i < n; ++i) dmax = fmax(dmax, sd[i]);
-    s_bounds[2] = dmax;   // lambda_max >= the largest diagonal entry
+  double lo0 = 1e300, hi0 = -1e300, emax2 = 0, dmax = 0;
+  for (int i = tid; i < n; i += ET) {
+    double r = (i > 0 ? se[i - 1] : 0.0) + (i + 1 < n ? se[i] : 0.0);
+    lo0 = fmin(lo0, sd[i] - r);
+    hi0 = fmax(hi0, sd[i] + r);
+    if (i + 1 < n) emax2 = fmax(emax2, se2[i]);
+    dmax = fmax(dmax, sd[i]);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    lo0 = fmin(lo0, __shfl_xor(lo0, o));
+    hi0 = fmax(hi0, __shfl_xor(hi0, o));
+    emax2 = fmax(emax2, __shfl_xor(emax2, o));
+    dmax = fmax(dmax, __shfl_xor(dmax, o));
+  }
+  if (lane == 0) {
+    s_b[0][wv] = lo0;
+    s_b[1][wv] = hi0;
+    s_b[2][wv] = emax2;
+    s_b[3][wv] = dmax;
   }
   __syncthreads();
-  const double glo = s_bounds[0], ghi = s_bounds[1];
-  // an eigenvalue whose bracket lies below zero_tol * (lower bound of lambda_max) is dropped
-  // whatever its exact value, so its bisection stops there
-  const double cut_lb = zero_tol * s_bounds[2];
+  for (int w = 0; w < ET / 64; ++w) {
+    lo0 = fmin(lo0, s_b[0][w]);
+    hi0 = fmax(hi0, s_b[1][w]);
+    emax2 = fmax(emax2, s_b[2][w]);
+    dmax = fmax(dmax, s_b[3][w]);
+  }
+  const double nrm = fmax(fabs(lo0), fabs(hi0));
+  const double glo = lo0 - (2 * DBL_EPSILON * nrm + 1e-300), ghi = hi0 + (2 * DBL_EPSILON * nrm + 1e-300);
+  // an eigenvalue whose bracket lies below zero_tol * (lower bound of lambda_max: the largest
+  // diagonal entry) is dropped whatever its exact value, so its bisection stops there
+  const double cut_lb = zero_tol * dmax;
   const double tnorm = fmax(fabs(glo), fabs(ghi));
-  double emax2 = 0;
-  for (int i = 0; i + 1 < n; ++i) emax2 = fmax(emax2, se2[i]);
   const double pivmin = DBL_MIN * fmax(1.0, emax2);
 
   // ---- shared multisection: the counts below 2 ET points (the Gershgorin ends and a
@@ -613,65 +676,119 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
       else if (p == NPT - 1 || !(lr > 0)) x[h] = ghi;
       else x[h] = fmin(ghi, fmax(glo, bot * exp(lr * (double)(p - 1) / (double)(NPT - 2))));
     }
-    int c0, c1;
-    sturm_count2(n, sd, se2, x[0], x[1], pivmin, c0, c1);
+    int c[2];
+    sturm_count<2>(n, sd, se2, x, pivmin, c);
     gx[2 * tid] = x[0];
     gx[2 * tid + 1] = x[1];
-    gc[2 * tid] = c0;
-    gc[2 * tid + 1] = c1;
+    gc[2 * tid] = c[0];
+    gc[2 * tid + 1] = c[1];
   }
   __syncthreads();
 
   // ---- bisection for the keep largest eigenvalues
-  for (int k = tid; k < keep; k += ET) {
-    const int idx = n - 1 - k;   // ascending index
+  const int g = tid & (G - 1), levels = G >= 16 ? 3 : G >= 4 ? 2 : 1;
+  const bool split = G == 8;                  // a lane per point, else a lane per bracket
+  const int nd = split ? g >> 1 : g;          // the lane's bracket
+  for (int kb = 0; kb < keep; kb += ET / G) {
+    const int k = kb + tid / G;
+    const bool real = k < keep;
+    const int idx = n - 1 - (real ? k : 0);   // ascending index
     // trisection: count(lo) <= idx < count(hi) is kept; start from the grid points (ascending,
     // counts nondecreasing) that bracket idx most tightly
     double lo = glo, hi = ghi;
-    for (int p = 0; p < 2 * ET; ++p) {
+    for (int p = g; p < 2 * ET; p += G) {
       if (gc[p] <= idx) lo = fmax(lo, gx[p]);
       else hi = fmin(hi, gx[p]);
     }
-    for (int it = 0; it < 140; ++it) {
-      const double w = hi - lo;
-      const double m1 = lo + w * (1.0 / 3.0), m2 = lo + w * (2.0 / 3.0);
-      if (w <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin || m1 <= lo || m2 >= hi || m2 <= m1 ||
-          hi <= cut_lb)
-        break;
-      int c1, c2;
-      sturm_count2(n, sd, se2, m1, m2, pivmin, c1, c2);
-      if (c1 > idx) hi = m1;
-      else if (c2 > idx) { lo = m1; hi = m2; }
-      else lo = m2;
+    for (int o = G >> 1; o > 0; o >>= 1) {
+      lo = fmax(lo, __shfl_xor(lo, o));
+      hi = fmin(hi, __shfl_xor(hi, o));
     }
-    ev[k] = 0.5 * (lo + hi);
+    auto third = [](double a, double b, double& m1, double& m2) {
+      const double w = b - a;
+      m1 = a + w * (1.0 / 3.0);
+      m2 = a + w * (2.0 / 3.0);
+    };
+    auto descend = [&](double& a, double& b, int s) {   // the first, middle or last third
+      double m1, m2;
+      third(a, b, m1, m2);
+      if (s == 0) b = m1;
+      else if (s == 1) { a = m1; b = m2; }
+      else a = m2;
+    };
+    bool live = real;
+    for (int it = 0; __any(live);) {
+      // the lane's node of the tree of brackets: node 0 the bracket itself, nodes 1 .. 3 its
+      // thirds, nodes 4 .. 12 theirs
+      double a = lo, b = hi;
+      if (nd >= 4) descend(a, b, (nd - 4) / 3);
+      if (nd >= 1) descend(a, b, (nd - 1) % 3);
+      double m1, m2;
+      third(a, b, m1, m2);
+      int c1, c2;
+      if (split) {
+        const double x[1] = {(g & 1) ? m2 : m1};
+        int c[1];
+        sturm_count<1>(n, sd, se2, x, pivmin, c);
+        c1 = c2 = c[0];
+      } else {
+        const double x[2] = {m1, m2};
+        int c[2];
+        sturm_count<2>(n, sd, se2, x, pivmin, c);
+        c1 = c[0];
+        c2 = c[1];
+      }
+      int node = 0;
+      for (int l = 0; l < levels; ++l) {
+        const int n1 = __shfl(c1, split ? 2 * node : node, G), n2 = __shfl(c2, split ? 2 * node + 1 : node, G);
+        const double w = hi - lo;
+        third(lo, hi, m1, m2);
+        if (it >= 140 || w <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin || m1 <= lo || m2 >= hi ||
+            m2 <= m1 || hi <= cut_lb)
+          live = false;
+        const int s = n1 > idx ? 0 : n2 > idx ? 1 : 2;
+        if (live) descend(lo, hi, s);
+        node = 3 * node + 1 + s;
+        ++it;
+      }
+    }
+    if (real && g == 0) sev[k] = 0.5 * (lo + hi);
   }
   __syncthreads();
-  const double lmax = ev[0];
+  if (tid == ET - 1) {
+    // the phases omega: a serial product, beside the vectors of the first waves
+    c64d w = {1.0, 0.0};
+    om[0] = w;
+#pragma unroll 8
+    for (int i = 0; i + 1 < n; ++i) {
+      if (se[i] > 0) w = w * sph[i];
+      om[i + 1] = w;
+    }
+  }
+  const double lmax = sev[0];
   const double cut = fmax(zero_tol * fmax(lmax, 0.0), 1e-300);
 
   // ---- clusters of relatively close kept eigenvalues (gap < 1e-3 of the eigenvalue):
   // their vectors are computed by one thread, each orthogonalised against the previous
   // members of its cluster after every solve.  Other eigenvalues are isolated relative to
   // their size, so inverse iteration alone yields vectors accurate to eps * lambda_max / gap.
-  __shared__ short cl_end[EMAX];
-  if (tid == 0) {
-    int k = 0;
-    while (k < keep) {
-      int e = k + 1;
-      while (e < keep && ev[e - 1] > cut && ev[e] > cut && (ev[e - 1] - ev[e]) < 1e-3 * ev[e - 1]) ++e;
-      for (int q = k; q < e; ++q) cl_end[q] = (short)(q == k ? e : -1);
-      k = e;
-    }
-  }
-  __syncthreads();
+  // joined(k): k is in the cluster of k - 1
+  auto joined = [&](int k) { return sev[k - 1] > cut && sev[k] > cut && (sev[k - 1] - sev[k]) < 1e-3 * sev[k - 1]; };
+  double* const F = LDSF ? dyn : Xg;
+  double* const X = F;
+  double* const U0 = F + nk;   // LU factors
+  double* const U1 = U0 + nk;
+  double* const U2 = U1 + nk;
+  double* const L = U2 + nk;
+  double* const PV = L + nk;
   for (int k0 = tid; k0 < keep; k0 += ET) {
-    const int kend = cl_end[k0];
-    if (kend < 0) continue;
+    if (k0 > 0 && joined(k0)) continue;
+    int kend = k0 + 1;
+    while (kend < keep && joined(kend)) ++kend;
     for (int k = k0; k < kend; ++k) {
-      const double lam = ev[k];
+      const double lam = sev[k];
       if (!(lam > cut)) {
-        for (int i = 0; i < n; ++i) X[(long long)i * keep + k] = 0.0;
+        for (int i = 0; i < n; ++i) Xg[(long long)i * keep + k] = 0.0;
         continue;
       }
       // perturbed shift so that the factorisation is never exactly singular
@@ -707,7 +824,6 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
       // last solve is accumulated as it is written.  U0 holds the reciprocal pivots, and the
       // factors are loaded CH steps at a time, so that the dependent chain of a solve waits
       // for memory once per chunk rather than once per step.
-      constexpr int CH = 4;
       double sc = 1.0, nn2 = 0.0;
       for (int itr = 0; itr < 2; ++itr) {
         if (itr > 0) {
@@ -715,14 +831,11 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
           for (int ib = 0; ib + 1 < n; ib += CH) {
             double xa[CH], pa[CH], la[CH];
 #pragma unroll
-            for (int q = 0; q < CH; ++q) {
-              const int i = ib + q;
-              if (i + 1 < n) {
-                const int o = i * keep + k;   // < 2^17
-                xa[q] = X[o + keep];
-                pa[q] = PV[o];
-                la[q] = L[o];
-              }
+            for (int q = 0; q < CH; ++q) {   // past the end: the last step's values, not used
+              const int o = min(ib + q, n - 2) * keep + k;   // < 2^17
+              xa[q] = X[o + keep];
+              pa[q] = PV[o];
+              la[q] = L[o];
             }
 #pragma unroll
             for (int q = 0; q < CH; ++q) {
@@ -744,14 +857,12 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
           double xa[CH], u0[CH], u1[CH], u2[CH];
 #pragma unroll
           for (int q = 0; q < CH; ++q) {
-            const int i = ib - q;
-            if (i >= 0) {
-              const int o = i * keep + k;   // < 2^17
-              xa[q] = itr == 0 ? 0.5 + (hash32((uint32_t)(i * 7919 + k * 104729 + 17)) >> 8) * (1.0 / 16777216.0) : X[o];
-              u0[q] = U0[o];
-              u1[q] = U1[o];
-              u2[q] = U2[o];
-            }
+            const int i = max(ib - q, 0);
+            const int o = i * keep + k;   // < 2^17
+            xa[q] = itr == 0 ? 0.5 + (hash32((uint32_t)(i * 7919 + k * 104729 + 17)) >> 8) * (1.0 / 16777216.0) : X[o];
+            u0[q] = U0[o];
+            u1[q] = U1[o];
+            u2[q] = U2[o];
           }
 #pragma unroll
           for (int q = 0; q < CH; ++q) {
@@ -785,7 +896,12 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
           }
         }
         const double inv = nn2 > 0 ? 1.0 / sqrt(nn2) : 0.0;
-        for (int i = 0; i < n; ++i) X[(long long)i * keep + k] *= inv;
+#pragma unroll 8
+        for (int i = 0; i < n; ++i) {
+          const double y = X[i * keep + k] * inv;
+          if (LDSF && kend > k0 + 1) X[i * keep + k] = y;   // read again by the rest of the cluster
+          Xg[i * keep + k] = y;
+        }
       }
     }
   }
@@ -793,8 +909,9 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, double zero_tol
   // zero the dropped eigenvalues, kept sum
   double s = 0;
   for (int k = tid; k < keep; k += ET) {
-    double lam = ev[k];
-    if (!(lam > cut)) { lam = 0.0; ev[k] = 0.0; }
+    double lam = sev[k];
+    if (!(lam > cut)) lam = 0.0;
+    ev[k] = lam;
     s += lam;
   }
   s = block_sum(s, red);
@@ -1379,8 +1496,16 @@ hipError_t heev_phase(int phase, int n, int keep, double zero_tol, void* A, long
       else hipLaunchKernelGGL((k_tridiag<512, 4, 2, 512>), dim3(batch), dim3(512), 0, st, n, (c64d*)A, sA, ws, sW, active);
       break;
     case 1:
-      hipLaunchKernelGGL(k_tri_eig, dim3(batch), dim3(ET), 0, st, n, keep, zero_tol, ws, sW, evals, sE, kept_sum, active);
+    {
+      const int G = keep <= 16 ? 16 : keep <= 32 ? 8 : keep <= 64 ? 4 : 1;
+      if ((long long)n * keep <= TRI_LDS_MAX)
+        hipLaunchKernelGGL((k_tri_eig<true, 8>), dim3(batch), dim3(ET), sizeof(double) * 6 * n * keep, st, n, keep, G, zero_tol, ws, sW, evals, sE, kept_sum, active);
+      else if (keep <= 64)
+        hipLaunchKernelGGL((k_tri_eig<false, 16>), dim3(batch), dim3(ET), 0, st, n, keep, G, zero_tol, ws, sW, evals, sE, kept_sum, active);
+      else
+        hipLaunchKernelGGL((k_tri_eig<false, 8>), dim3(batch), dim3(ET), 0, st, n, keep, G, zero_tol, ws, sW, evals, sE, kept_sum, active);
       break;
+    }
     case 2:
       if (n <= 128) hipLaunchKernelGGL((k_tri_orth<128>), dim3(batch), dim3(ET), 0, st, n, keep, ws, sW, evals, sE, active);
       else if (n <= 256) hipLaunchKernelGGL((k_tri_orth<256>), dim3(batch), dim3(ET), 0, st, n, keep, ws, sW, evals, sE, active);

@@ -600,7 +600,7 @@ __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, int G, double z
                                                 double* __restrict__ evals, long long sE, double* __restrict__ kept_sum,
                                                 const int* __restrict__ active) {
   if (active && !active[blockIdx.x]) return;
-  extern __shared__ double dyn[];   // LDSF: X, U0, U1, U2, L, PV [n][keep]
+  extern __shared__ __align__(16) double dyn[];   // LDSF: X, U0, U1, U2, L, PV [n][keep]
   __shared__ double sd[EMAX], se[EMAX], se2[EMAX];
   __shared__ c64d sph[EMAX];   // phases of the subdiagonal
   __shared__ double sev[EMAX / 2];   // the kept eigenvalues
@@ -1105,128 +1105,219 @@ __global__ __launch_bounds__(ET) void k_tri_orth(int n, int keep, double* __rest
 
 // ---------------------------------------------------------------------------- E3
 // evec = Q diag(omega) X, Q = H_0 ... H_{n-3} with u_j in column j below the diagonal;
-// reflectors are applied in blocks of NB from the last block to the first as
-// (I - V T V^dag), with V staged in LDS.  Thread c owns column c of Z (and, when keep is
-// smaller than the workgroup, one of several row slices of it).
-template <int NMAX, int NB>
-__global__ __launch_bounds__(ET) void k_backtransform(int n, int keep, const c64d* __restrict__ Ag, long long sA,
-                                                      double* __restrict__ ws, long long sW,
-                                                      c64d* __restrict__ Zg, long long sZ, const int* __restrict__ mask) {
-  if (mask && !mask[blockIdx.x]) return;
-  __shared__ c64d Vb[NMAX][NB];
-  __shared__ c64d Tm[NB][NB];
-  __shared__ c64d Sv[NB][NB];
-  __shared__ c64d Wred[ET][NB];
-  const c64d* A = Ag + blockIdx.x * sA;
-  double* W = ws + blockIdx.x * sW;
-  const c64d* om = (const c64d*)(W + 4 * n);
-  const double* X = W + 6 * n;
-  c64d* Z = Zg + blockIdx.x * sZ;
-  const int tid = threadIdx.x;
-  const int nslice = keep >= ET ? 1 : ET / keep;           // row slices per column
-  const int c = tid % keep, slice = tid / keep;
-  const bool active = tid < keep * nslice;
-  // Z = diag(omega) X
-  for (int i = tid; i < n * keep; i += ET) {
-    const int r = i / keep;
-    const double x = X[i];
-    Z[i] = c64d{om[r].re * x, om[r].im * x};
+// reflectors are applied in blocks of 16 from the last block to the first as (I - V T V^dag).
+// workspace per matrix: d, e, trace, omega, X and the inverse-iteration arrays (6 n + 6 n keep
+// doubles), then the T factors (2 * 16 * 16 doubles per block of 16 reflectors)
+__host__ __device__ inline size_t bt_tfac_offset(int n, int keep) { return (size_t)6 * n + (size_t)6 * n * keep + 64; }
+
+// lane L of each row of 16 lanes, in every lane of the row (DPP row_newbcast)
+template <int L>
+__device__ inline double row_bcast16(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + L, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + L, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// element (a, b), a < b, of S = V^dag V over the rows below j0
+__device__ inline c64d bt_gram(const c64d (*Vb)[16], int a, int b, int j0, int n) {
+  c64d s = {0, 0};
+#pragma unroll 4
+  for (int i = j0 + 1; i < n; ++i) s = s + cmulc(Vb[i][a], Vb[i][b]);
+  return s;
+}
+
+// row a of the compact-WY factor T from S: a row needs nothing of the others, so each lane
+// keeps its own in registers (entries left of the diagonal are zeros that add nothing)
+__device__ inline void bt_trow(const c64d (*Sv)[16], int a, int nb, c64d (&T)[16]) {
+#pragma unroll
+  for (int jj = 0; jj < 16; ++jj) {
+    T[jj] = c64d{0, 0};
+    if (jj < nb) {
+      c64d s = {0, 0};
+#pragma unroll
+      for (int b = 0; b < jj; ++b) s = s + T[b] * Sv[b][jj];
+      s = -2.0 * s;
+      T[jj] = jj > a ? s : c64d{jj == a ? 2.0 : 0.0, 0.0};
+    }
+  }
+}
+
+// T factors of all blocks, one workgroup per block (34 < n <= 128)
+__global__ __launch_bounds__(256) void k_bt_tfac_small(int n, const c64d* __restrict__ Ag, long long sA, double* __restrict__ ws,
+                                                       long long sW, int keep, int nblk, const int* __restrict__ active) {
+  const int mat = blockIdx.x / nblk, blk = blockIdx.x - mat * nblk;
+  if (active && !active[mat]) return;
+  __shared__ c64d Vb[128][16];
+  __shared__ c64d Sv[16][16];
+  const c64d* A = Ag + mat * sA;
+  c64d* Tout = (c64d*)(ws + mat * sW + bt_tfac_offset(n, keep)) + (long long)blk * 256;
+  const int tid = threadIdx.x, j0 = 16 * blk, nb = min(16, n - 2 - j0);
+  for (int e = 16 * (j0 + 1) + tid; e < n * 16; e += 256) {
+    const int i = e >> 4, a = e & 15, ja = j0 + a;
+    Vb[i][a] = (a < nb && i > ja) ? A[(long long)i * n + ja] : c64d{0, 0};
   }
   __syncthreads();
+  {
+    const int a = tid >> 4, b = tid & 15;
+    Sv[a][b] = a < b ? bt_gram(Vb, a, b, j0, n) : c64d{0, 0};
+  }
+  __syncthreads();
+  if (tid < 16) {
+    c64d T[16];
+    bt_trow(Sv, tid, nb, T);
+#pragma unroll
+    for (int b = 0; b < 16; ++b) Tout[tid * 16 + b] = T[b];
+  }
+}
+
+// s = row of T (t: its element of this lane of 16) times the column wt; the zeros left of the
+// diagonal and past the block's reflectors add nothing
+template <int B>
+__device__ inline void bt_tw(c64d& s, c64d t, const c64d* wt, int stride) {
+  if constexpr (B < 16) {
+    const c64d u{row_bcast16<B>(t.re), row_bcast16<B>(t.im)}, x = wt[B * stride];
+    s.re += fma(u.re, x.re, -(u.im * x.im));
+    s.im += fma(u.im, x.re, u.re * x.im);
+    bt_tw<B + 1>(s, t, wt, stride);
+  }
+}
+
+// n <= 128: a workgroup holds a panel of 16 columns of Z in LDS beside the current block of V and
+// applies the blocks to it, so that the chip sees (keep / 16) x batch workgroups and Z is written
+// once.  W = V^dag Z is summed over 256 / keep row slices, each in ascending rows, the slices in
+// ascending order; a wave takes whole slices, a lane 2 x 2 elements of W (4 LDS reads for 4
+// complex products).  FUSE: T of each block is made here: at one or two blocks that costs less
+// than the second launch (n = 32: 18 us in all), otherwise it is read from the workspace.
+// Bound by the five dependent stages of a block.  Against one workgroup per matrix with Z in
+// global memory: n = 26 x 60 76 -> 17 us, 32 x 15 97 -> 18, 64 x 15 163 -> 27, 128 x 15 383 -> 55,
+// 100 x 500 585 -> 316, 128 x 512 826 -> 421 (two workgroups per CU by 128 registers: spills, 486).
+constexpr int BTS_NT = 512;
+template <bool FUSE>
+__global__ __launch_bounds__(BTS_NT) void k_bt_small(int n, int keep, const c64d* __restrict__ Ag, long long sA,
+                                                     const double* __restrict__ ws, long long sW, c64d* __restrict__ Zg,
+                                                     long long sZ, int n_panels, const int* __restrict__ mask) {
+  extern __shared__ __align__(16) double dyn[];   // V [n][16], Z [n][16], W [slice][16][min(keep, 16)]
+  __shared__ c64d Sv[FUSE ? 16 : 1][16];
+  __shared__ c64d Tm[FUSE ? 16 : 1][16];
+  // the panels of a matrix are consecutive logical ids on one XCD
+  const int G = gridDim.x, w = blockIdx.x;
+  const int q8 = G >> 3, r8 = G & 7, x8 = w & 7;
+  const int L = x8 * q8 + min(x8, r8) + (w >> 3);
+  const int mat = L / n_panels, panel = L - mat * n_panels;
+  if (mask && !mask[mat]) return;
+  c64d(*Vb)[16] = (c64d(*)[16])dyn;
+  c64d(*Zp)[16] = Vb + n;
+  c64d* Wq = (c64d*)(Zp + n);
+  const c64d* A = Ag + mat * sA;
+  const double* W = ws + mat * sW;
+  const c64d* om = (const c64d*)(W + 4 * n);
+  const double* X = W + 6 * n;
+  const c64d* Tg = (const c64d*)(W + bt_tfac_offset(n, keep));
+  c64d* Z = Zg + mat * sZ;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int c0 = panel * 16, pc = min(16, keep - c0), pcw = min(16, keep);
+  const int nslice = ET / keep;
   const int nref = n - 2;
-  if (nref <= 0) return;
-  const int nblk = (nref + NB - 1) / NB;
+  const int nblk = nref > 0 ? (nref + 15) / 16 : 0;
+  c64d vn[4];   // the next block's V
+  auto load_v = [&](int j0) {
+    const int nb = min(16, nref - j0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + u * BTS_NT, i = e >> 4, a = e & 15, ja = j0 + a;
+      vn[u] = (i < n && a < nb && i > ja) ? A[(long long)i * n + ja] : c64d{0, 0};
+    }
+  };
+  if (nblk > 0) load_v(16 * (nblk - 1));
+  // Z = diag(omega) X
+  for (int e = tid; e < n * 16; e += BTS_NT) {
+    const int r = e >> 4, c = e & 15;
+    const double x = c < pc ? X[(long long)r * keep + c0 + c] : 0.0;
+    Zp[r][c] = c64d{om[r].re * x, om[r].im * x};
+  }
   for (int blk = nblk - 1; blk >= 0; --blk) {
-    const int j0 = blk * NB, nb = min(NB, nref - j0);
-    for (int e = tid; e < n * NB; e += ET) {
-      const int i = e / NB, a = e % NB;
-      const int ja = j0 + a;
-      Vb[i][a] = (a < nb && i > ja) ? A[(long long)i * n + ja] : c64d{0, 0};
+    const int j0 = 16 * blk, nb = min(16, nref - j0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = tid + u * BTS_NT;
+      if (e < n * 16) Vb[e >> 4][e & 15] = vn[u];
     }
+    c64d t = {0, 0};   // element (tid / 16, tid % 16) of T
+    if (!FUSE && tid < 256) t = Tg[(long long)blk * 256 + tid];
     __syncthreads();
-    for (int e = tid; e < nb * nb; e += ET) {
-      const int a = e / nb, b = e % nb;
-      c64d s = {0, 0};
-      for (int i = j0 + 1; i < n; ++i) s = s + cmulc(Vb[i][a], Vb[i][b]);
-      Sv[a][b] = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < NB * NB; e += ET) Tm[e / NB][e % NB] = c64d{0, 0};
-    __syncthreads();
-    for (int jj = 0; jj < nb; ++jj) {
-      if (tid < jj) {
-        const int a = tid;
-        c64d s = {0, 0};
-        for (int b = a; b < jj; ++b) s = s + Tm[a][b] * Sv[b][jj];
-        Tm[a][jj] = -2.0 * s;
+    if (blk > 0) load_v(j0 - 16);
+    if constexpr (FUSE) {
+      if (tid < 256) {
+        const int a = tid >> 4, b = tid & 15;
+        Sv[a][b] = a < b ? bt_gram(Vb, a, b, j0, n) : c64d{0, 0};
       }
-      if (tid == 0) Tm[jj][jj] = c64d{2.0, 0.0};
       __syncthreads();
-    }
-    // Wt = V^dag Z (column c, partial over this thread's row slice)
-    c64d acc[NB];
+      if (wv == 7) {
+        c64d T[16];
+        bt_trow(Sv, lane & 15, nb, T);
+        if (lane < 16) {
 #pragma unroll
-    for (int a = 0; a < NB; ++a) acc[a] = c64d{0, 0};
-    if (active) {
-      int i = j0 + 1 + slice;
-      for (; i + 3 * nslice < n; i += 4 * nslice) {
-        c64d z[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) z[u] = Z[(long long)(i + u * nslice) * keep + c];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int a = 0; a < NB; ++a) acc[a] = acc[a] + cmulc(Vb[i + u * nslice][a], z[u]);
-      }
-      for (; i < n; i += nslice) {
-        const c64d z = Z[(long long)i * keep + c];
-#pragma unroll
-        for (int a = 0; a < NB; ++a) acc[a] = acc[a] + cmulc(Vb[i][a], z);
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < NB; ++a) Wred[tid][a] = acc[a];
-    __syncthreads();
-    c64d wt[NB];
-    if (active) {
-#pragma unroll
-      for (int a = 0; a < NB; ++a) {
-        c64d s = {0, 0};
-        for (int q = 0; q < nslice; ++q) s = s + Wred[q * keep + c][a];
-        wt[a] = s;
-      }
-      // wt <- T wt
-      c64d tw[NB];
-#pragma unroll
-      for (int a = 0; a < NB; ++a) {
-        c64d s = {0, 0};
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          if (b >= a && b < nb) s = s + Tm[a][b] * wt[b];
-        tw[a] = s;
-      }
-      // Z -= V tw
-      int i = j0 + 1 + slice;
-      for (; i + 3 * nslice < n; i += 4 * nslice) {
-        c64d z[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) z[u] = Z[(long long)(i + u * nslice) * keep + c];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          c64d s = {0, 0};
-#pragma unroll
-          for (int a = 0; a < NB; ++a) s = s + Vb[i + u * nslice][a] * tw[a];
-          Z[(long long)(i + u * nslice) * keep + c] = z[u] - s;
+          for (int b = 0; b < 16; ++b) Tm[lane][b] = T[b];
         }
       }
-      for (; i < n; i += nslice) {
-        c64d s = {0, 0};
+    }
+    // W = V^dag Z
+    const int NWV = FUSE ? 7 : 8;   // FUSE: the last wave is making T
+    if (!FUSE || wv < 7) {
+      const int cp = lane & 7, ap = lane >> 3;
+      for (int q = wv; q < nslice; q += NWV) {
+        c64d acc[2][2] = {{{0, 0}, {0, 0}}, {{0, 0}, {0, 0}}};
+#pragma unroll 2
+        for (int i = j0 + 1 + q; i < n; i += nslice) {
+          const c64d z0 = Zp[i][cp], z1 = Zp[i][cp + 8], v0 = Vb[i][ap], v1 = Vb[i][ap + 8];
+          acc[0][0] = acc[0][0] + cmulc(v0, z0);
+          acc[0][1] = acc[0][1] + cmulc(v0, z1);
+          acc[1][0] = acc[1][0] + cmulc(v1, z0);
+          acc[1][1] = acc[1][1] + cmulc(v1, z1);
+        }
 #pragma unroll
-        for (int a = 0; a < NB; ++a) s = s + Vb[i][a] * tw[a];
-        Z[(long long)i * keep + c] = Z[(long long)i * keep + c] - s;
+        for (int x = 0; x < 4; ++x) {
+          const int a = ap + 8 * (x >> 1), c = cp + 8 * (x & 1);
+          if (c < pcw) Wq[(q * 16 + a) * pcw + c] = acc[x >> 1][x & 1];
+        }
       }
     }
     __syncthreads();
+    const int ra = tid >> 4, rc = tid & 15;
+    const bool red = tid < 256 && rc < pcw;
+    if (red) {
+      c64d s = {0, 0};
+      for (int q = 0; q < nslice; ++q) s = s + Wq[(q * 16 + ra) * pcw + rc];
+      Wq[ra * pcw + rc] = s;
+    }
+    __syncthreads();
+    // W <- T W, into slice 1 (keep <= 128: there are at least two)
+    if (tid < 256) {
+      if (FUSE) t = Tm[FUSE ? ra : 0][rc];
+      c64d s = {0, 0};
+      bt_tw<0>(s, t, Wq + min(rc, pcw - 1), pcw);
+      if (red) Wq[(16 + ra) * pcw + rc] = s;
+    }
+    __syncthreads();
+    // Z -= V W
+    {
+      c64d tw[16];
+#pragma unroll
+      for (int a = 0; a < 16; ++a) tw[a] = Wq[(16 + a) * pcw + min(rc, pcw - 1)];
+      for (int i = j0 + 1 + ra; i < n; i += BTS_NT / 16) {
+        c64d s = {0, 0};
+#pragma unroll
+        for (int a = 0; a < 16; ++a) s = s + Vb[i][a] * tw[a];
+        Zp[i][rc] = Zp[i][rc] - s;
+      }
+    }
+    __syncthreads();
+  }
+  if (nblk == 0) __syncthreads();
+  for (int e = tid; e < n * 16; e += BTS_NT) {
+    const int r = e >> 4, c = e & 15;
+    if (c < pc) Z[(long long)r * keep + c0 + c] = Zp[r][c];
   }
 }
 
@@ -1240,10 +1331,6 @@ __global__ __launch_bounds__(ET) void k_backtransform(int n, int keep, const c64
 // numbered so that they run on one XCD); the panel is written out once.
 // MFMA lane layout (f64 16x16x4): A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
 // D[i][j] in lane j + 16 (i % 4), register i / 4.
-// workspace per matrix: d, e, trace, omega, X and the inverse-iteration arrays (6 n + 6 n keep
-// doubles), then the T factors (2 * 16 * 16 doubles per block of 16 reflectors)
-__host__ __device__ inline size_t bt_tfac_offset(int n, int keep) { return (size_t)6 * n + (size_t)6 * n * keep + 64; }
-
 __global__ __launch_bounds__(256) void k_bt_tfac(int n, const c64d* __restrict__ Ag, long long sA, double* __restrict__ ws,
                                                  long long sW, int keep, const int* __restrict__ active) {
   if (active && !active[blockIdx.x]) return;
@@ -1512,15 +1599,23 @@ hipError_t heev_phase(int phase, int n, int keep, double zero_tol, void* A, long
       else hipLaunchKernelGGL((k_tri_orth<512>), dim3(batch), dim3(ET), 0, st, n, keep, ws, sW, evals, sE, active);
       break;
     default: {
-      if (n <= 128) {   // blocked LDS form
-        hipLaunchKernelGGL((k_backtransform<256, 16>), dim3(batch), dim3(ET), 0, st, n, keep, (const c64d*)A, sA, ws, sW, (c64d*)Z, sZ, active);
+      const int np = (keep + 15) / 16;
+      const long long blocks = (long long)np * batch;
+      if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+      if (n <= 128) {   // LDS panel form
+        const size_t lds = sizeof(c64d) * 16 * ((size_t)2 * n + (size_t)(ET / keep) * (keep < 16 ? keep : 16));
+        const int nblk = n > 2 ? (n - 2 + 15) / 16 : 0;
+        if (nblk <= 2) {
+          hipLaunchKernelGGL((k_bt_small<true>), dim3((unsigned)blocks), dim3(BTS_NT), lds, st, n, keep, (const c64d*)A, sA, ws, sW, (c64d*)Z, sZ, np, active);
+          break;
+        }
+        if ((long long)nblk * batch > 0x7fffffffLL) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_bt_tfac_small, dim3(nblk * batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, nblk, active);
+        hipLaunchKernelGGL((k_bt_small<false>), dim3((unsigned)blocks), dim3(BTS_NT), lds, st, n, keep, (const c64d*)A, sA, ws, sW, (c64d*)Z, sZ, np, active);
         break;
       }
       // 128 < n <= 512: MFMA panel form (T factors, then 16-column panels)
       hipLaunchKernelGGL(k_bt_tfac, dim3(batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, active);
-      const int np = (keep + 15) / 16;
-      const long long blocks = (long long)np * batch;
-      if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
       if (n <= 256)
         hipLaunchKernelGGL((k_bt_panel<256, 512>), dim3((unsigned)blocks), dim3(512), 0, st, n, keep, (const c64d*)A, sA, ws, sW, (c64d*)Z, sZ, np, active);
       else

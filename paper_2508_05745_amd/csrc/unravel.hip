@@ -1,7 +1,6 @@
 // Locally entanglement-optimal unravelling of single-qubit noise (FP64, one thread per
 // noise event), the counter-based branch sampler, the per-gate event kernel of the
-// trajectory sweep, the batched unravel_opt entry, and the differentiable unravelling cost
-// with its hand-written adjoint.
+// trajectory sweep and Born sampling.  (The batched unravel_opt entry: unravel_batch.hip.)
 //
 // Steps of the optimal mixing (Sec. "Locally entanglement-optimal unraveling", appendix
 // "Practical/closed-form version"):
@@ -19,14 +18,9 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "unravel_small.h"
 
 namespace mpsb {
-
-using cd = c64d;
-
-// ------------------------------------------------------------------ small helpers
-__device__ inline cd cz() { return cd{0.0, 0.0}; }
-__device__ inline double cabs_(cd a) { return sqrt(norm2(a)); }
 
 // cyclic Jacobi eigen-decomposition of a real symmetric n x n matrix (n <= NMAX), in place:
 // on exit a holds the eigenvalues on its diagonal, v the eigenvectors (columns).  The sweeps run
@@ -99,25 +93,10 @@ __device__ void jacobi_sym(int n, double (&a_io)[NMAX][NMAX], double (&v_io)[NMA
       }
 }
 
-__device__ inline cd yy_flip(const cd (&v)[4], int i) {
-  // (Y x Y) v*:  [ -v3*, v2*, v1*, -v0* ]
-  switch (i) {
-    case 0: return cd{-v[3].re, v[3].im};
-    case 1: return cd{v[2].re, -v[2].im};
-    case 2: return cd{v[1].re, -v[1].im};
-    default: return cd{-v[0].re, v[0].im};
-  }
-}
-
-struct UnravelOut {
-  cd W[4][4];     // [i][j], i < r: K'_j = sum_i W[i][j] K_i
-  double p[4];
-  double conc;
-  int separable;
-};
-
 // ------------------------------------------------------------------ the optimal mixing
-__device__ void optimal_mixing(const cd (&rho)[2][2], const cd (&K)[4][2][2], int r, UnravelOut& out) {
+// (not inlined: the compiler's choice of fused operations, and with it the last place of a
+// trajectory's branch operators, would follow the callers' code)
+__device__ __attribute__((noinline)) void optimal_mixing(const cd (&rho)[2][2], const cd (&K)[4][2][2], int r, UnravelOut& out) {
   // Psi_eff = sqrt(rho) for a 2x2 PSD matrix: (rho + sqrt(det) I) / sqrt(tr + 2 sqrt(det))
   double tr = rho[0][0].re + rho[1][1].re;
   double det = rho[0][0].re * rho[1][1].re - norm2(rho[0][1]);
@@ -799,60 +778,6 @@ __global__ __launch_bounds__(64) void k_site_event_check(EventArgs ea, const dou
   choose_mixing(ea.mode, rho, K, rr, Uf, W, conc);
   mixed_ops(K, rr, W, rho, Kp, p);
   if (!(p[forced[traj]] > 0.0)) atomicOr(status, 2);
-}
-
-// ------------------------------------------------------------------ unravel_opt
-// An item whose channel id lies outside 0..n_k-1 reads no channel: its U, p and eof are NaN.
-__global__ __launch_bounds__(64) void k_unravel_opt(int batch, const double* __restrict__ rho_q, const double* __restrict__ kraus,
-                              int n_k, const int* __restrict__ kraus_id, int r, double* __restrict__ U,
-                              double* __restrict__ p_out, double* __restrict__ eof) {
-  int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
-  const int kid = kraus_id ? kraus_id[b] : 0;
-  if (kid < 0 || kid >= n_k) {
-    const double nan = __builtin_nan("");
-    for (int j = 0; j < 4; ++j) {
-      p_out[b * 4 + j] = nan;
-      for (int i = 0; i < 2 * r; ++i) U[((long long)b * 4 + j) * r * 2 + i] = nan;
-    }
-    eof[b] = nan;
-    return;
-  }
-  cd rho[2][2];
-  for (int x = 0; x < 4; ++x) rho[x >> 1][x & 1] = cd{rho_q[b * 8 + 2 * x], rho_q[b * 8 + 2 * x + 1]};
-  cd K[4][2][2];
-  for (int i = 0; i < 4; ++i)
-    for (int a = 0; a < 2; ++a)
-      for (int c = 0; c < 2; ++c) {
-        if (i < r) {
-          const double* kp = kraus + ((long long)kid * r + i) * 8 + 2 * (2 * a + c);
-          K[i][a][c] = cd{kp[0], kp[1]};
-        } else K[i][a][c] = cz();
-      }
-  UnravelOut o;
-  optimal_mixing(rho, K, r, o);
-  cd Kp[4][2][2];
-  double p[4];
-  mixed_ops(K, r, o.W, rho, Kp, p);
-  for (int j = 0; j < 4; ++j) {
-    p_out[b * 4 + j] = p[j];
-    for (int i = 0; i < r; ++i) {
-      U[((long long)b * 4 + j) * r * 2 + 2 * i] = o.W[i][j].re;
-      U[((long long)b * 4 + j) * r * 2 + 2 * i + 1] = o.W[i][j].im;
-    }
-  }
-  double c = fmin(fmax(o.conc, 0.0), 1.0);
-  double x = 0.5 * (1.0 + sqrt(fmax(0.0, 1.0 - c * c)));
-  double h = 0;
-  if (x > 0 && x < 1) h = -x * log2(x) - (1 - x) * log2(1 - x);
-  eof[b] = h;
-}
-
-hipError_t launch_unravel_opt(int batch, const double* rho_q, const double* kraus, int n_k, const int* kraus_id, int r,
-                              double* U, double* p, double* eof, hipStream_t st) {
-  hipLaunchKernelGGL(k_unravel_opt, dim3((batch + 63) / 64), dim3(64), 0, st, batch, rho_q, kraus, n_k, kraus_id, r, U, p,
-                     eof);
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ Born sampling

@@ -341,40 +341,92 @@ hipError_t bond_moments(int batch, const void* theta, int chi_l, int chi_r, int 
 
 // ------------------------------------------------------------------ 4 x 4 matrices on 16 lanes
 // A state's 4 x 4 complex matrices are spread over a group of 16 lanes: lane g of the group
-// holds entry (g >> 2, g & 3).  Products exchange rows and columns by lane shuffles within the
-// group (no per-lane 4 x 4 or 8 x 8 arrays, which would not fit in registers).  Every lane of a
-// group follows the same control flow (group-uniform loop counts).
+// holds entry (g >> 2, g & 3) (no per-lane 4 x 4 or 8 x 8 arrays, which would not fit in
+// registers).  Every lane of a group follows the same control flow (group-uniform loop counts).
+// A group is one DPP row: the entries of a lane's matrix row come by quad broadcasts, so that a
+// product by a fixed right factor (its column kept in registers, Col) needs no LDS shuffle; the
+// products of the squarings take one skewed row by shuffle and the columns by row rotations.
+// What bounds eval and grad is this chain of products (bytes: 1.2 KB a state).  Against eight
+// shuffles a product, degree 18 and a division a term, eval / grad: 300 states 11.2 / 28.5 ->
+// 5.3 / 11.8 us, 65536 states 127 / 375 -> 45 / 133 us (bond 127 / 410 -> 49 / 158 us); grad at 168
+// or 128 registers for more waves spills.
 __device__ inline cd gsh(cd x, int src) { return cd{__shfl(x.re, src, 16), __shfl(x.im, src, 16)}; }
 
-__device__ inline cd gmm(cd a, cd b, int g) {   // (A B)[i][j]
-  const int i = g >> 2, j = g & 3;
+template <int CTRL>
+__device__ inline double dpp(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// entry (i, K) of the lane's matrix row i
+template <int K>
+__device__ inline cd grow(cd x) { return cd{dpp<K * 0x55>(x.re), dpp<K * 0x55>(x.im)}; }
+// entry (i + M mod 4, j)
+template <int M>
+__device__ inline cd gdown(cd x) {
+  if constexpr (M == 0) return x;
+  else return cd{dpp<0x120 + 16 - 4 * M>(x.re), dpp<0x120 + 16 - 4 * M>(x.im)};
+}
+
+struct Col { cd e[4]; };   // column j of a matrix, in every lane (i, j)
+__device__ inline Col gcol(cd x, int g) {
+  Col c;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c.e[k] = gsh(x, 4 * k + (g & 3));
+  return c;
+}
+__device__ inline void gacc(cd& s, cd a, const Col& b) {   // s += (A B)[i][j]
+  cfma(s, grow<0>(a), b.e[0]);
+  cfma(s, grow<1>(a), b.e[1]);
+  cfma(s, grow<2>(a), b.e[2]);
+  cfma(s, grow<3>(a), b.e[3]);
+}
+__device__ inline cd gmm(cd a, const Col& b) {
   cd s = {0, 0};
-  for (int k = 0; k < 4; ++k) cfma(s, gsh(a, 4 * i + k), gsh(b, 4 * k + j));
+  gacc(s, a, b);
   return s;
+}
+// entry (i, i + j mod 4): the row, skewed, so that grow<M> of it meets gdown<M> of the right factor
+__device__ inline cd gskew(cd a, int g) { return gsh(a, (g & 12) | (((g >> 2) + g) & 3)); }
+__device__ inline void gacc_skew(cd& s, cd ask, cd b) {   // s += A B, A skewed
+  cfma(s, grow<0>(ask), b);
+  cfma(s, grow<1>(ask), gdown<1>(b));
+  cfma(s, grow<2>(ask), gdown<2>(b));
+  cfma(s, grow<3>(ask), gdown<3>(b));
 }
 
 // max over the columns of the column sums of v (v >= 0 per entry), in every lane of the group
 __device__ inline double gcolmax(double v) {
-  v += __shfl_xor(v, 4, 16);
-  v += __shfl_xor(v, 8, 16);
-  v = fmax(v, __shfl_xor(v, 1, 16));
-  return fmax(v, __shfl_xor(v, 2, 16));
+  v += dpp<0x124>(v);
+  v += dpp<0x128>(v);
+  v = fmax(v, dpp<0xb1>(v));         // lanes 1 0 3 2 of the quad
+  return fmax(v, dpp<0x4e>(v));      // lanes 2 3 0 1
 }
 
-// exp(A) by scaling and squaring with a degree-18 Taylor polynomial (||A / 2^s||_1 <= 1/4)
-__device__ cd gexpm(cd a, int g) {
+// exp(A) by scaling and squaring with a degree-16 Taylor polynomial: ||A / 2^s||_1 <= 1/2, so
+// that the next term is below 3e-20 (for the Frechet derivative, whose term k carries k / k!,
+// below 8e-19 of ||E / 2^s||); a squaring less than from 1/4, each doubling the rounding error
+constexpr int TAYLOR = 16;
+__device__ inline cd gexpm(cd a, int g) {
   double nrm = gcolmax(sqrt(norm2(a)));
   int s = 0;
-  while (nrm > 0.25 && s < 60) { nrm *= 0.5; ++s; }
+  while (nrm > 0.5 && s < 60) { nrm *= 0.5; ++s; }
   const double sc = ldexp(1.0, -s);
   const cd x = sc * a;
   const cd one = (g >> 2) == (g & 3) ? cd{1, 0} : cd{0, 0};
-  cd term = one, out = one;
-  for (int k = 1; k <= 18; ++k) {
-    term = (1.0 / k) * gmm(term, x, g);
+  const Col xc = gcol(x, g);
+  cd term = x, out = one + x;
+#pragma unroll
+  for (int k = 2; k <= TAYLOR; ++k) {
+    term = (1.0 / k) * gmm(term, xc);
     out = out + term;
   }
-  for (int r = 0; r < s; ++r) out = gmm(out, out, g);
+  for (int r = 0; r < s; ++r) {
+    cd q = {0, 0};
+    gacc_skew(q, gskew(out, g), out);
+    out = q;
+  }
   return out;
 }
 
@@ -383,25 +435,32 @@ __device__ cd gexpm(cd a, int g) {
 // kept in its 4 x 4 blocks: term_k = [[T_k, F_k], [0, T_k]] with T_k = T_{k-1} A / k,
 // F_k = (F_{k-1} A + T_{k-1} E) / k, and a squaring maps [[P, Q], [0, P]] to
 // [[P^2, P Q + Q P], [0, P^2]].
-__device__ cd gfrechet(cd a, cd e, int g) {
+__device__ inline cd gfrechet(cd a, cd e, int g) {
   double nrm = gcolmax(sqrt(norm2(a)) + sqrt(norm2(e)));
   int s = 0;
-  while (nrm > 0.25 && s < 60) { nrm *= 0.5; ++s; }
+  while (nrm > 0.5 && s < 60) { nrm *= 0.5; ++s; }
   const double sc = ldexp(1.0, -s);
   const cd x = sc * a, y = sc * e;
   const cd one = (g >> 2) == (g & 3) ? cd{1, 0} : cd{0, 0};
-  cd T = one, F = {0, 0}, P = one, Q = {0, 0};
-  for (int k = 1; k <= 18; ++k) {
+  const Col xc = gcol(x, g), yc = gcol(y, g);
+  cd T = x, F = y, P = one + x, Q = y;
+#pragma unroll
+  for (int k = 2; k <= TAYLOR; ++k) {
     const double f = 1.0 / k;
-    const cd Fn = f * (gmm(F, x, g) + gmm(T, y, g));
-    T = f * gmm(T, x, g);
+    const cd Fn = f * (gmm(F, xc) + gmm(T, yc));
+    T = f * gmm(T, xc);
     F = Fn;
     P = P + T;
     Q = Q + F;
   }
   for (int r = 0; r < s; ++r) {
-    Q = gmm(P, Q, g) + gmm(Q, P, g);
-    P = gmm(P, P, g);
+    const cd ps = gskew(P, g), qs = gskew(Q, g);
+    cd pq = {0, 0}, qp = {0, 0}, pp = {0, 0};
+    gacc_skew(pq, ps, Q);
+    gacc_skew(qp, qs, P);
+    gacc_skew(pp, ps, P);
+    Q = pq + qp;
+    P = pp;
   }
   return Q;
 }
@@ -450,12 +509,13 @@ __device__ __forceinline__ void branch_setup(int g, const double* rho_in, const 
   const cd x = cd{-br.h.im, br.h.re};   // iH
   const cd ex = gexpm(x, g);
   // U = exp(iH) U_ref
-  cd u = {0, 0};
-  for (int k = 0; k < 4; ++k) cfma(u, gsh(ex, 4 * a + k), cd{uref[2 * (4 * k + c)], uref[2 * (4 * k + c) + 1]});
+  Col uc;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) uc.e[k] = cd{uref[2 * (4 * k + c)], uref[2 * (4 * k + c) + 1]};
+  const cd u = gmm(ex, uc);
   br.U = u;
   // branch j = a: K'_j = sum_m U_jm K_m
-  cd row[4];
-  for (int m = 0; m < 4; ++m) row[m] = gsh(u, 4 * a + m);
+  const cd row[4] = {grow<0>(u), grow<1>(u), grow<2>(u), grow<3>(u)};
   for (int x2 = 0; x2 < 2; ++x2)
     for (int y = 0; y < 2; ++y) {
       cd s = {0, 0};
@@ -505,10 +565,10 @@ __global__ __launch_bounds__(256) void k_cost_eval(int batch, const double* rho,
   if (br.p > P_TINY) term = kind == 0 ? br.p - br.P / br.p : -br.p * log(br.P / (br.p * br.p)) / LN2;
   // the 4 lanes of row j hold branch j's term: a quarter from each, summed over the group
   double v = 0.25 * term;
-  v += __shfl_xor(v, 1, 16);
-  v += __shfl_xor(v, 2, 16);
-  v += __shfl_xor(v, 4, 16);
-  v += __shfl_xor(v, 8, 16);
+  v += dpp<0xb1>(v);
+  v += dpp<0x4e>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x128>(v);
   if (g == 0 && b < batch) f[b] = v;
 }
 

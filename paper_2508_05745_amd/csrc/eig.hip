@@ -1331,22 +1331,25 @@ __global__ __launch_bounds__(BTS_NT) void k_bt_small(int n, int keep, const c64d
 // numbered so that they run on one XCD); the panel is written out once.
 // MFMA lane layout (f64 16x16x4): A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
 // D[i][j] in lane j + 16 (i % 4), register i / 4.
+// E3a: parts workgroups per matrix, each every parts-th block; a row of T per lane, in registers.
+// A block is a chain (S, then 120 products); one workgroup per matrix for all blocks left the chip
+// idle below about 1024 matrices.  E3a + E3b, matrix n x batch: 256 x 15 290 -> 114 us, 256 x 256
+// 822 -> 685, 512 x 192 4.70 -> 4.32 ms; 256 x 1024 (one part) 2.59 -> 2.63 ms.
 __global__ __launch_bounds__(256) void k_bt_tfac(int n, const c64d* __restrict__ Ag, long long sA, double* __restrict__ ws,
-                                                 long long sW, int keep, const int* __restrict__ active) {
-  if (active && !active[blockIdx.x]) return;
+                                                 long long sW, int keep, int parts, const int* __restrict__ active) {
+  const int mat = blockIdx.x / parts, part = blockIdx.x - mat * parts;
+  if (active && !active[mat]) return;
   __shared__ double Sp[4][2][16][16];
   __shared__ c64d Sv[16][16];
-  __shared__ c64d Tm[16][16];
-  const c64d* A = Ag + blockIdx.x * sA;
-  double* W = ws + blockIdx.x * sW;
-  c64d* Tout = (c64d*)(W + bt_tfac_offset(n, keep));
+  const c64d* A = Ag + mat * sA;
+  c64d* Tg = (c64d*)(ws + mat * sW + bt_tfac_offset(n, keep));
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r16 = lane & 15, kq = lane >> 4;
-  const int nref = n - 2;
-  const int nblk = nref > 0 ? (nref + 15) / 16 : 0;
-  for (int blk = 0; blk < nblk; ++blk) {
-    const int j0 = 16 * blk, nb = min(16, nref - j0);
+  const int nblk = (n - 2 + 15) / 16;
+  for (int blk = part; blk < nblk; blk += parts) {
+    const int j0 = 16 * blk, nb = min(16, n - 2 - j0);
     // S[a][b] = sum_i conj(V[i][a]) V[i][b]; lane r16 + 16 kq holds V[row][r16] for both operands
     v4d_t sr = {0, 0, 0, 0}, si = {0, 0, 0, 0};
+#pragma unroll 4
     for (int i0 = j0 + 1 + 4 * wv; i0 < n; i0 += 16) {
       const int row = i0 + kq;
       c64d v = {0, 0};
@@ -1366,21 +1369,15 @@ __global__ __launch_bounds__(256) void k_bt_tfac(int n, const c64d* __restrict__
       const int a = tid >> 4, b = tid & 15;
       Sv[a][b] = c64d{Sp[0][0][a][b] + Sp[1][0][a][b] + Sp[2][0][a][b] + Sp[3][0][a][b],
                       Sp[0][1][a][b] + Sp[1][1][a][b] + Sp[2][1][a][b] + Sp[3][1][a][b]};
-      Tm[a][b] = c64d{0, 0};
     }
     __syncthreads();
-    for (int jj = 0; jj < nb; ++jj) {
-      if (tid < jj) {
-        const int a = tid;
-        c64d s = {0, 0};
-        for (int b = a; b < jj; ++b) s = s + Tm[a][b] * Sv[b][jj];
-        Tm[a][jj] = -2.0 * s;
-      }
-      if (tid == 0) Tm[jj][jj] = c64d{2.0, 0.0};
-      __syncthreads();
+    if (tid < 16) {
+      c64d T[16];
+      bt_trow(Sv, tid, nb, T);
+#pragma unroll
+      for (int b = 0; b < 16; ++b) Tg[(long long)blk * 256 + tid * 16 + b] = T[b];
     }
-    Tout[(long long)blk * 256 + tid] = Tm[tid >> 4][tid & 15];
-    __syncthreads();
+    // (the next block writes Sv two barriers from here, after this wave has read it)
   }
 }
 
@@ -1615,7 +1612,9 @@ hipError_t heev_phase(int phase, int n, int keep, double zero_tol, void* A, long
         break;
       }
       // 128 < n <= 512: MFMA panel form (T factors, then 16-column panels)
-      hipLaunchKernelGGL(k_bt_tfac, dim3(batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, active);
+      // about 1024 workgroups for the T factors
+      const int nblk = (n - 2 + 15) / 16, parts = batch >= 1024 ? 1 : min(nblk, 1024 / batch);
+      hipLaunchKernelGGL(k_bt_tfac, dim3(parts * batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, parts, active);
       if (n <= 256)
         hipLaunchKernelGGL((k_bt_panel<256, 512>), dim3((unsigned)blocks), dim3(512), 0, st, n, keep, (const c64d*)A, sA, ws, sW, (c64d*)Z, sZ, np, active);
       else

@@ -273,10 +273,13 @@ __global__ __launch_bounds__(64 * NW, 2) void k_bond_moments(int chi_l, int chi_
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  // fixed-order reduction: within each wave by shuffles, then the waves in order
+  // fixed-order reduction: within each wave by shuffles, then the waves in order (unrolled: indexed
+  // at run time the moments would live in scratch memory, read and written by every fold; 16384
+  // FP32 states of chi 64 2.64 -> 2.18 ms, 300 118 -> 104 us, 4096 FP64 states of chi 45 432 -> 349 us)
   __shared__ double red[NW][36];
+#pragma unroll
   for (int x = 0; x < 36; ++x) {
-    double s = x < 16 ? ms[x] : (x < 32 ? mb[x - 16] : r[x - 32]);
+    double s = x < 16 ? ms[x & 15] : (x < 32 ? mb[x & 15] : r[x & 3]);
     for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
     if (lane == 0) red[wv][x] = s;
   }

@@ -499,43 +499,66 @@ __device__ __attribute__((noinline)) void optimal_mixing(const cd (&rho)[2][2], 
   out.separable = cdiff > 0.0 ? 0 : 1;
 }
 
+// The events' complex products with the fused operations written out: left to the compiler their
+// form, and with it the last place of a trajectory's branch operators, would follow the code
+// around them.
+__device__ inline cd mulx(cd a, cd b) { return cd{fma(a.re, b.re, -(a.im * b.im)), fma(a.im, b.re, a.re * b.im)}; }
+__device__ inline cd mulxc(cd a, cd b) { return cd{fma(a.re, b.re, a.im * b.im), fma(a.im, b.re, -(a.re * b.im))}; }   // a conj(b)
+
 // K'_j, p_j = Tr(K'_j rho K'_j^dag)
-__device__ void mixed_ops(const cd (&K)[4][2][2], int r, const cd (&W)[4][4], const cd (&rho)[2][2],
-                          cd (&Kp)[4][2][2], double (&p)[4]) {
+__device__ inline void mixed_ops(const cd (&K)[4][2][2], int r, const cd (&W)[4][4], const cd (&rho)[2][2],
+                                 cd (&Kp)[4][2][2], double (&p)[4]) {
+#pragma unroll
   for (int j = 0; j < 4; ++j) {
+#pragma unroll
     for (int a = 0; a < 2; ++a)
+#pragma unroll
       for (int b = 0; b < 2; ++b) {
         cd acc = cz();
-        for (int i = 0; i < r; ++i) cfma(acc, W[i][j], K[i][a][b]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i < r) acc = acc + mulx(W[i][j], K[i][a][b]);
         Kp[j][a][b] = acc;
       }
     double s = 0;
+#pragma unroll
     for (int a = 0; a < 2; ++a) {
       // (K rho K^dag)[a][a] = sum_{m,n} K[a][m] rho[m][n] conj(K[a][n])
-      cd acc = cz();
+      double acc = 0;
+#pragma unroll
       for (int m = 0; m < 2; ++m)
-        for (int nn = 0; nn < 2; ++nn) acc = acc + Kp[j][a][m] * rho[m][nn] * conj(Kp[j][a][nn]);
-      s += acc.re;
+#pragma unroll
+        for (int nn = 0; nn < 2; ++nn) {
+          const cd t = mulx(Kp[j][a][m], rho[m][nn]), k = Kp[j][a][nn];
+          // (which product is rounded first is part of the weight's last place, and so of every
+          // recorded run: the imaginary one, but for this term of the branches after the first)
+          acc += j > 0 && m == 0 && nn == 1 ? fma(t.im, k.im, t.re * k.re) : fma(t.re, k.re, t.im * k.im);
+        }
+      s += acc;
     }
     p[j] = fmax(s, 0.0);
   }
 }
 
-__device__ void choose_mixing(int mode, const cd (&rho)[2][2], const cd (&K)[4][2][2], int r, const cd (&Ufix)[4][4],
-                              cd (&W)[4][4], double& conc) {
+// OPT: state-dependent mixings (mode 3) are possible; without it the eigensolvers drop out
+template <bool OPT>
+__device__ inline void choose_mixing(int mode, const cd (&rho)[2][2], const cd (&K)[4][2][2], int r, const cd (&Ufix)[4][4],
+                                     cd (&W)[4][4], double& conc) {
   conc = -1.0;
-  if (mode == 3) {
+  if (OPT && mode == 3) {
     UnravelOut o;
     optimal_mixing(rho, K, r, o);
+#pragma unroll
     for (int i = 0; i < 4; ++i)
+#pragma unroll
       for (int j = 0; j < 4; ++j) W[i][j] = o.W[i][j];
     conc = o.conc;
-  } else if (mode == 1) {
-    for (int i = 0; i < 4; ++i)
-      for (int j = 0; j < 4; ++j) W[i][j] = (i < r) ? Ufix[j][i] : cz();
   } else {
+    const bool fix = mode == 1;
+#pragma unroll
     for (int i = 0; i < 4; ++i)
-      for (int j = 0; j < 4; ++j) W[i][j] = (i == j && i < r) ? cd{1.0, 0.0} : cz();
+#pragma unroll
+      for (int j = 0; j < 4; ++j) W[i][j] = i < r ? (fix ? Ufix[j][i] : cd{i == j ? 1.0 : 0.0, 0.0}) : cz();
   }
 }
 
@@ -552,14 +575,17 @@ __device__ inline double event_uniform(uint64_t seed, uint32_t traj, uint32_t la
 }
 __device__ inline int sample_branch(const double (&p)[4], double u) {
   double total = 0;
+#pragma unroll
   for (int j = 0; j < 4; ++j) total += p[j];
   double acc = 0;
   int last = -1;
+  bool hit = false;
+#pragma unroll
   for (int j = 0; j < 4; ++j) {
     acc += p[j];
-    if (p[j] > 0.0) {
+    if (!hit && p[j] > 0.0) {
       last = j;
-      if (u < acc / total) return j;
+      hit = u < acc / total;
     }
   }
   return last;
@@ -570,21 +596,26 @@ __device__ inline int sample_branch(const double (&p)[4], double u) {
 
 // Channel of an event: table entry `id` when the launch reads the circuit tables, else the
 // by-value slot `slot` (0: lower / single qubit, 1: upper qubit of a gate).
-__device__ void load_channel(const EventArgs& ea, int slot, int id, cd (&K)[4][2][2], int& r, cd (&Uf)[4][4]) {
-  const double* kd = ea.ev_ids ? ea.kraus_tab + 32LL * id : ea.kraus[slot];
-  const double* ud = ea.ev_ids ? (ea.fixed_tab ? ea.fixed_tab + 32LL * id : nullptr) : ea.fixed_u[slot];
-  r = ea.ev_ids ? ea.nk_tab[id] : ea.n_kraus[slot];
-  for (int i = 0; i < 4; ++i)
-    for (int a = 0; a < 2; ++a)
-      for (int b = 0; b < 2; ++b) {
-        int o = 2 * (4 * i + 2 * a + b);
-        K[i][a][b] = cd{kd[o], kd[o + 1]};
-      }
-  for (int j = 0; j < 4; ++j)
-    for (int i = 0; i < 4; ++i) {
-      int o = 2 * (4 * j + i);
-      Uf[j][i] = ud ? cd{ud[o], ud[o + 1]} : cz();
+__device__ inline void load_channel(const EventArgs& ea, int slot, int id, cd (&K)[4][2][2], int& r, cd (&Uf)[4][4]) {
+  // (two branches: a pointer that may lead to the kernel's arguments or to a table would put a
+  // copy of the arguments into per-lane scratch)
+  if (ea.ev_ids) {
+    const double* kd = ea.kraus_tab + 32LL * id;
+    const double* ud = ea.fixed_tab ? ea.fixed_tab + 32LL * id : nullptr;
+    r = ea.nk_tab[id];
+#pragma unroll
+    for (int o = 0; o < 16; ++o) {
+      K[o >> 2][(o >> 1) & 1][o & 1] = cd{kd[2 * o], kd[2 * o + 1]};
+      Uf[o >> 2][o & 3] = ud ? cd{ud[2 * o], ud[2 * o + 1]} : cz();
     }
+  } else {
+    r = ea.n_kraus[slot];
+#pragma unroll
+    for (int o = 0; o < 16; ++o) {
+      K[o >> 2][(o >> 1) & 1][o & 1] = cd{ea.kraus[slot][2 * o], ea.kraus[slot][2 * o + 1]};
+      Uf[o >> 2][o & 3] = cd{ea.fixed_u[slot][2 * o], ea.fixed_u[slot][2 * o + 1]};
+    }
+  }
 }
 
 __device__ inline int current_layer(const EventArgs& ea) { return ea.layer_ptr ? *ea.layer_ptr : ea.layer; }
@@ -596,9 +627,19 @@ __device__ inline int event_channel(const EventArgs& ea, int traj, int layer, in
   return slot_present ? 0 : -1;
 }
 
+// entry j of a register array
+__device__ inline double pick(const double (&p)[4], int j) {
+  double v = p[0];
+#pragma unroll
+  for (int t = 1; t < 4; ++t)
+    if (t == j) v = p[t];
+  return v;
+}
+
 // One noise event on a normalised single-qubit reduced state: choose W, p, draw, return the
 // selected operator.  Returns -1 on a forced zero-probability branch.
-__device__ int one_event(const EventArgs& ea, int slot, int id, const cd (&rho)[2][2], uint32_t traj, uint32_t layer,
+template <bool OPT>
+__device__ inline int one_event(const EventArgs& ea, int slot, int id, const cd (&rho)[2][2], uint32_t traj, uint32_t layer,
                          uint32_t qubit, int forced, cd (&Ksel)[2][2], double (&p)[4], cd (&W)[4][4]) {
   cd K[4][2][2], Uf[4][4], Kp[4][2][2];
   int r;
@@ -606,18 +647,20 @@ __device__ int one_event(const EventArgs& ea, int slot, int id, const cd (&rho)[
   const long long ridx = (long long)traj * ea.rec_stride + ((int)qubit - ea.rec_qbase);
   if (ea.w_in) {   // replayed mixing: W[i][j] = U[j][i]
     const double* w = ea.w_in + ridx * 32;
+#pragma unroll
     for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
       for (int i = 0; i < 4; ++i) W[i][jj] = cd{w[2 * (4 * jj + i)], w[2 * (4 * jj + i) + 1]};
   } else {
     double conc;
-    choose_mixing(ea.mode, rho, K, r, Uf, W, conc);
+    choose_mixing<OPT>(ea.mode, rho, K, r, Uf, W, conc);
   }
   mixed_ops(K, r, W, rho, Kp, p);
   if (ea.branch_in && forced < 0) forced = ea.branch_in[ridx];
   int j;
   if (forced >= 0) {
     j = forced;
-    if (j > 3 || !(p[j] > 0.0)) return -1;
+    if (j > 3 || !(pick(p, j) > 0.0)) return -1;
   } else {
     j = sample_branch(p, event_uniform(ea.seed, (uint32_t)(ea.traj_base + (long long)traj), layer, qubit));
     // no branch of positive weight (a zero or non-finite state): nothing is selected
@@ -627,9 +670,17 @@ __device__ int one_event(const EventArgs& ea, int slot, int id, const cd (&rho)[
       return -2;
     }
   }
-  double inv = 1.0 / sqrt(p[j]);
+  double inv = 1.0 / sqrt(pick(p, j));
+#pragma unroll
   for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) Ksel[a][b] = inv * Kp[j][a][b];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      cd k = Kp[0][a][b];
+#pragma unroll
+      for (int t = 1; t < 4; ++t)
+        if (t == j) k = Kp[t][a][b];
+      Ksel[a][b] = inv * k;
+    }
   return j;
 }
 
@@ -639,7 +690,9 @@ __device__ void write_record(const EventArgs& ea, int traj, int qubit, int j, co
   if (ea.w_out) {
     double* w = ea.w_out + idx * 32;
     // U[j][i] = W[i][j]
+#pragma unroll
     for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
       for (int i = 0; i < 4; ++i) {
         w[2 * (4 * jj + i)] = W[i][jj].re;
         w[2 * (4 * jj + i) + 1] = W[i][jj].im;
@@ -650,66 +703,94 @@ __device__ void write_record(const EventArgs& ea, int traj, int qubit, int j, co
 // Gate events: reduce the theta tiles' RDM partials (fixed order), then the events of the
 // lower and upper qubit; writes kops[traj] = {Ks, Kt} (normalised by 1/sqrt(p)).
 constexpr int EV_SPREAD = 8;
-__global__ __launch_bounds__(64) void k_gate_events(EventArgs ea, const double* __restrict__ partial, int n_tiles, int q, int has_s, int has_t,
+template <bool OPT>
+__global__ __launch_bounds__(64) __attribute__((flatten)) void k_gate_events(EventArgs ea, const double* __restrict__ partial, int n_tiles, int q, int has_s, int has_t,
                               double* __restrict__ kops, int* __restrict__ status) {
+#pragma clang fp contract(off)   // fused operations are written out (see mulx)
   // EV_SPREAD trajectories per wave (one lane each, the other lanes idle): the per-lane work
   // is a long dependent chain (the small eigensolvers of two noise events) with a large
   // register footprint, so spreading the waves over all CUs shortens the launch; 8 per wave
-  // measured fastest (16 leaves half the CUs idle, 4 and 2 add waves without gain)
+  // measured fastest (16 leaves half the CUs idle, 4 and 2 add waves without gain).  All lanes sum
+  // the tiles' partials; without OPT everything stays in registers (1.9 KB of scratch a lane while
+  // arrays were indexed at run time).  Two events of 1000 trajectories: 38 -> 23 us, optimal 326 ->
+  // 308; 1024 trajectories with 64 tiles 76 -> 31 us, optimal 364 -> 321.
+  __shared__ double rs8[EV_SPREAD][32];
+  // the tiles' partial sums, one of the 32 numbers of a trajectory per lane
+  for (int e = threadIdx.x; e < EV_SPREAD * 32; e += 64) {
+    const int tr = blockIdx.x * EV_SPREAD + (e >> 5);
+    double s = 0;
+    if (tr < ea.n_traj) {
+      const double* pp = partial + (long long)tr * n_tiles * 32 + (e & 31);
+#pragma unroll 4
+      for (int t = 0; t < n_tiles; ++t) s += pp[t * 32];
+    }
+    rs8[e >> 5][e & 31] = s;
+  }
+  __syncthreads();
   if (threadIdx.x % (64 / EV_SPREAD)) return;
   int traj = blockIdx.x * EV_SPREAD + threadIdx.x / (64 / EV_SPREAD);
   if (traj >= ea.n_traj) return;
   const int layer = current_layer(ea);
   const int ch_s = event_channel(ea, traj, layer, q, has_s), ch_t = event_channel(ea, traj, layer, q + 1, has_t);
   cd rho[4][4];
-  for (int x = 0; x < 16; ++x) rho[x >> 2][x & 3] = cz();
-  const double* pp = partial + (long long)traj * n_tiles * 32;
-  for (int t = 0; t < n_tiles; ++t)
-    for (int x = 0; x < 16; ++x) {
-      rho[x >> 2][x & 3].re += pp[t * 32 + 2 * x];
-      rho[x >> 2][x & 3].im += pp[t * 32 + 2 * x + 1];
-    }
+  const double* rp = rs8[threadIdx.x / (64 / EV_SPREAD)];
+#pragma unroll
+  for (int x = 0; x < 16; ++x) rho[x >> 2][x & 3] = cd{rp[2 * x], rp[2 * x + 1]};
   double tr = rho[0][0].re + rho[1][1].re + rho[2][2].re + rho[3][3].re;
   if (!(tr > 0.0) || !isfinite(tr)) { atomicOr(status, 1); tr = 1.0; }
-  for (int x = 0; x < 16; ++x) rho[x >> 2][x & 3] = (1.0 / tr) * rho[x >> 2][x & 3];
+  const cd r02 = rho[0][2], r20 = rho[2][0];   // unnormalised
+  const double it = 1.0 / tr;
+#pragma unroll
+  for (int x = 0; x < 16; ++x) rho[x >> 2][x & 3] = it * rho[x >> 2][x & 3];
   cd Ks[2][2] = {{{1, 0}, {0, 0}}, {{0, 0}, {1, 0}}}, Kt[2][2] = {{{1, 0}, {0, 0}}, {{0, 0}, {1, 0}}};
   double p[4];
   cd W[4][4];
   if (ch_s >= 0) {
-    cd rs[2][2];
-    for (int s = 0; s < 2; ++s)
-      for (int s2 = 0; s2 < 2; ++s2) rs[s][s2] = rho[2 * s][2 * s2] + rho[2 * s + 1][2 * s2 + 1];
-    int j = one_event(ea, 0, ch_s, rs, traj, layer, q, -1, Ks, p, W);
+    const cd rs[2][2] = {{rho[0][0] + rho[1][1], cd{fma(it, r02.re, rho[1][3].re), fma(it, r02.im, rho[1][3].im)}},
+                         {cd{fma(it, r20.re, rho[3][1].re), fma(it, r20.im, rho[3][1].im)}, rho[2][2] + rho[3][3]}};
+    int j = one_event<OPT>(ea, 0, ch_s, rs, traj, layer, q, -1, Ks, p, W);
     if (j < 0) { atomicOr(status, j == -1 ? 2 : 1); j = 0; }
     write_record(ea, traj, q, j, W);
     // rho <- (Ks x I) rho (Ks x I)^dag  (Ks already carries 1/sqrt(p))
     cd t1[4][4];
+#pragma unroll
     for (int a = 0; a < 4; ++a)
+#pragma unroll
       for (int b = 0; b < 4; ++b) {
         cd acc = cz();
-        for (int s0 = 0; s0 < 2; ++s0) cfma(acc, Ks[a >> 1][s0], rho[2 * s0 + (a & 1)][b]);
+#pragma unroll
+        for (int s0 = 0; s0 < 2; ++s0) acc = acc + mulx(Ks[a >> 1][s0], rho[2 * s0 + (a & 1)][b]);
         t1[a][b] = acc;
       }
+#pragma unroll
     for (int a = 0; a < 4; ++a)
+#pragma unroll
       for (int b = 0; b < 4; ++b) {
         cd acc = cz();
-        for (int s0 = 0; s0 < 2; ++s0) cfma_conj(acc, t1[a][2 * s0 + (b & 1)], Ks[b >> 1][s0]);
+#pragma unroll
+        for (int s0 = 0; s0 < 2; ++s0) acc = acc + mulxc(t1[a][2 * s0 + (b & 1)], Ks[b >> 1][s0]);
         rho[a][b] = acc;
       }
   }
   if (ch_t >= 0) {
     cd rt[2][2];
+#pragma unroll
     for (int t = 0; t < 2; ++t)
+#pragma unroll
       for (int t2 = 0; t2 < 2; ++t2) rt[t][t2] = rho[t][t2] + rho[2 + t][2 + t2];
     double tt = rt[0][0].re + rt[1][1].re;
+#pragma unroll
     for (int a = 0; a < 2; ++a)
+#pragma unroll
       for (int b = 0; b < 2; ++b) rt[a][b] = (1.0 / tt) * rt[a][b];
-    int j = one_event(ea, 1, ch_t, rt, traj, layer, q + 1, -1, Kt, p, W);
+    int j = one_event<OPT>(ea, 1, ch_t, rt, traj, layer, q + 1, -1, Kt, p, W);
     if (j < 0) { atomicOr(status, j == -1 ? 2 : 1); j = 0; }
     write_record(ea, traj, q + 1, j, W);
   }
   double* ko = kops + (long long)traj * 16;
+#pragma unroll
   for (int a = 0; a < 2; ++a)
+#pragma unroll
     for (int b = 0; b < 2; ++b) {
       ko[2 * (2 * a + b)] = Ks[a][b].re;
       ko[2 * (2 * a + b) + 1] = Ks[a][b].im;
@@ -741,7 +822,7 @@ __global__ __launch_bounds__(64) void k_site_event(EventArgs ea, const double* _
   double p[4];
   cd W[4][4];
   int f = forced ? forced[traj] : -1;
-  int j = one_event(ea, ch, id, rho, traj, layer, q, f, Ks, p, W);
+  int j = one_event<true>(ea, ch, id, rho, traj, layer, q, f, Ks, p, W);
   if (j < 0) {
     atomicOr(status, j == -1 ? 2 : 1);
     Ks[0][0] = cd{1, 0}; Ks[0][1] = cz(); Ks[1][0] = cz(); Ks[1][1] = cd{1, 0};
@@ -775,7 +856,7 @@ __global__ __launch_bounds__(64) void k_site_event_check(EventArgs ea, const dou
   int rr;
   load_channel(ea, ch, 0, K, rr, Uf);
   double conc, p[4];
-  choose_mixing(ea.mode, rho, K, rr, Uf, W, conc);
+  choose_mixing<true>(ea.mode, rho, K, rr, Uf, W, conc);
   mixed_ops(K, rr, W, rho, Kp, p);
   if (!(p[forced[traj]] > 0.0)) atomicOr(status, 2);
 }
@@ -837,8 +918,12 @@ hipError_t born_step(int prec, const void* W, long long sW, int S, int dr, void*
 
 hipError_t launch_gate_events(const EventArgs& ea, const double* partial, int n_tiles, int q, int has_s, int has_t,
                               double* kops, int* status, hipStream_t st) {
-  hipLaunchKernelGGL(k_gate_events, dim3((ea.n_traj + EV_SPREAD - 1) / EV_SPREAD), dim3(64), 0, st, ea, partial, n_tiles, q, has_s, has_t,
-                     kops, status);
+  // state-independent mixings need no eigensolver
+  const dim3 grid((ea.n_traj + EV_SPREAD - 1) / EV_SPREAD);
+  if (ea.mode == 3)
+    hipLaunchKernelGGL(k_gate_events<true>, grid, dim3(64), 0, st, ea, partial, n_tiles, q, has_s, has_t, kops, status);
+  else
+    hipLaunchKernelGGL(k_gate_events<false>, grid, dim3(64), 0, st, ea, partial, n_tiles, q, has_s, has_t, kops, status);
   return hipGetLastError();
 }
 

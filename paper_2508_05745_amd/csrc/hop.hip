@@ -78,8 +78,11 @@ __device__ inline void inv_cols(c64d (&x)[16], int ii, const double* ipiv) {
 // 15 of n = 32 58 -> 39, n = 64 118 -> 84, n = 128 334 -> 254.  At n = 128 a workgroup spends a
 // third of that in the product with R^-1 (two thirds of its matrix-core time), a quarter in the
 // panels and a fifth in the inverse's block columns.
+// Registers: 128 up to 64 columns, for four workgroups per CU (160 without the spills: 15 of
+// n = 64 84 -> 79 us, but 1024 of n = 40 97 -> 116); 224 at 96, where LDS leaves room for two
+// (against 128 with 0.5 KB of scratch: 15 of n = 96 238 -> 156 us, 500 459 -> 345, 2048 1800 -> 1404).
 template <typename T, int NMAX, int HT>
-__global__ __launch_bounds__(HT, NMAX > 96 ? 2 : 4) void k_hop_chol(int n, int left_to_right, int other, const c64d* __restrict__ Eg,
+__global__ __launch_bounds__(HT, NMAX > 64 ? 2 : 4) void k_hop_chol(int n, int left_to_right, int other, const c64d* __restrict__ Eg,
                                                  long long sE, cplx<T>* __restrict__ C, long long sC,
                                                  cplx<T>* __restrict__ Rout, long long sR, double tol) {
   __shared__ c64d R[NMAX * (NMAX + 1) / 2];

@@ -399,9 +399,13 @@ __device__ inline void gacc_skew(cd& s, cd ask, cd b) {   // s += A B, A skewed
   cfma(s, grow<3>(ask), gdown<3>(b));
 }
 
-// max over the columns of the column sums of v (v >= 0 per entry), in every lane of the group
+// max over the columns of the column sums of v (v >= 0 per entry), the same bits in every lane of
+// the group: lanes of one group must choose the same number of squarings.  So each lane adds the
+// rows 0 + 1 and 2 + 3 first (lane ^ 4 is the half-row mirror, 7 - lane, of the reversed quad;
+// lane ^ 8 a rotation by 8).  Rotations by 4 and 8 would add (0 + 3) + (2 + 1) in some rows and
+// (1 + 0) + (3 + 2) in others, and a norm at a power of two would split the group.
 __device__ inline double gcolmax(double v) {
-  v += dpp<0x124>(v);
+  v += dpp<0x141>(dpp<0x1b>(v));
   v += dpp<0x128>(v);
   v = fmax(v, dpp<0xb1>(v));         // lanes 1 0 3 2 of the quad
   return fmax(v, dpp<0x4e>(v));      // lanes 2 3 0 1

@@ -374,10 +374,11 @@ int hop_right(mpsb_batch* h, int j) {
     double* C1 = W<double>(h, L.o_tmp);
     double* C2 = C1 + 2LL * rows * 128;
     double* Tq = W<double>(h, L.o_x);
+    // the factors by their own sizes, 128^2 + 2 128 n2 + n2^2 = bj^2 elements of the s_wm >= cr^2
     double* R11 = W<double>(h, L.o_rm);
-    double* R22 = R11 + 2 * 128 * 128;
-    double* R12 = R22 + 2 * 128 * 128;
-    double* S = R12 + 2 * 128 * 128;
+    double* R12 = R11 + 2 * 128 * 128;
+    double* S = R12 + 2LL * 128 * n2;
+    double* R22 = S + 2LL * 128 * n2;
     char* Cjc = (char*)Cj;
     HIPCHK(remap(1, C1, L.s_tmp, 128, rows, 128, 128, rows, 128, Cjc, L.s_traj, cr, 0, false, nullptr, T, h->st));
     HIPCHK(remap(1, C2, L.s_tmp, n2, rows, n2, n2, rows, n2, Cjc + 128 * 16, L.s_traj, cr, 0, false, nullptr, T, h->st));
@@ -473,10 +474,11 @@ int hop_left(mpsb_batch* h, int j) {
     double* C1 = W<double>(h, L.o_tmp);
     double* C2 = C1 + 2LL * 128 * cols;
     double* Tq = W<double>(h, L.o_x);
+    // laid out as in hop_right, bj^2 elements of the s_wm >= cl^2
     double* R11 = W<double>(h, L.o_rm);
-    double* R22 = R11 + 2 * 128 * 128;
-    double* S1 = R22 + 2 * 128 * 128;   // (C2 Q1^dag), n2 x 128
-    double* S = S1 + 2 * 128 * 128;
+    double* S1 = R11 + 2 * 128 * 128;   // (C2 Q1^dag), n2 x 128
+    double* S = S1 + 2LL * 128 * n2;
+    double* R22 = S + 2LL * 128 * n2;
     char* Cjc = (char*)Cj;
     HIPCHK(remap(1, C1, L.s_tmp, cols, 128, cols, br, 128, br, Cjc, L.s_traj, 2 * cr, cr, false, nullptr, T, h->st));
     HIPCHK(remap(1, C2, L.s_tmp, cols, n2, cols, br, n2, br, Cjc + (size_t)128 * 2 * cr * 16, L.s_traj, 2 * cr, cr, false,

@@ -31,3 +31,20 @@ def test_truncation_at_instance_edges(chi, n, depth):
         assert np.abs(disc - np.array(eps)).max() < 1e-10
         truncated += int((np.array(eps) > 1e-9).sum())
     assert truncated > 0
+
+
+@pytest.mark.parametrize("chi,n,depth", [(129, 16, 10), (140, 17, 10), (192, 17, 11), (255, 18, 12)])
+def test_two_block_hops(chi, n, depth):
+    """Centre hops of 129 to 255 columns, whose two blocks share a workspace of chi^2 elements per
+    trajectory: two trajectories, so that a factor outside its place shows in its neighbour too."""
+    from paper_2508_05745_amd import mpsb as M
+    c = I.brickwork(n, depth, seed=700 + chi, channel=I.dephasing(0.1))
+    out = run_gpu(c, chi, 2, 91, M.FP64, M.ORTHOGONAL, record=True)
+    truncated = 0
+    for t in range(2):
+        ref, eps = oracle_obs_mps(c, chi, t, 91, M.ORTHOGONAL)
+        disc = np.concatenate([out["disc"][l][t, : len(c.pairs(l))][:: 1 if l % 2 == 0 else -1] for l in range(depth)])
+        assert np.abs(out["per_traj"][t] - ref).max() < 1e-10
+        assert np.abs(disc - np.array(eps)).max() < 1e-10
+        truncated += int((np.array(eps) > 1e-9).sum())
+    assert truncated > 0

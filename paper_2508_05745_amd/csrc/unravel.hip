@@ -94,6 +94,9 @@ __device__ void jacobi_sym(int n, double (&a_io)[NMAX][NMAX], double (&v_io)[NMA
 }
 
 // ------------------------------------------------------------------ the optimal mixing
+// moduli below this have squares that lose digits to underflow (sqrt(DBL_MIN / DBL_EPSILON))
+constexpr double G_TINY = 1e-146;
+
 // (not inlined: the compiler's choice of fused operations, and with it the last place of a
 // trajectory's branch operators, would follow the callers' code)
 __device__ __attribute__((noinline)) void optimal_mixing(const cd (&rho)[2][2], const cd (&K)[4][2][2], int r, UnravelOut& out) {
@@ -145,6 +148,15 @@ __device__ __attribute__((noinline)) void optimal_mixing(const cd (&rho)[2][2], 
         if (g <= 2.0 * DBL_EPSILON * sqrt(al * be) || g == 0.0) continue;
         rotated = true;
         cd eph = {ga.re / g, -ga.im / g};   // e^{-i phi}
+        if (g < G_TINY) {
+          // the columns of a product state can be parallel: the rotations shrink the remainder by
+          // eps a sweep, down to overlaps whose square underflows.  An angle from such a g turns by
+          // less than it should, a phase from it would not be one: scaled
+          const double m = fmax(fabs(ga.re), fabs(ga.im));
+          const cd u = {ga.re / m, ga.im / m};
+          const double n = cabs_(u);
+          eph = cd{u.re / n, -u.im / n};
+        }
         double zeta = (be - al) / (2.0 * g);
         double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
         double c = 1.0 / sqrt(1.0 + t * t), s = c * t;

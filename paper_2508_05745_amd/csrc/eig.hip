@@ -25,7 +25,7 @@ namespace mpsb {
 
 constexpr int ET = 256;           // threads per workgroup
 constexpr int EMAX = 512;         // largest matrix dimension
-constexpr int TRI_LDS_MAX = 2048; // n keep up to which the inverse iteration runs in LDS
+constexpr int TRI_LDS_MAX = 2048; // n keep up to which the inverse iteration may run in LDS (48 bytes each)
 
 // Cross-lane moves of doubles on the VALU, without the LDS crossbar: DPP within rows of 16
 // lanes (quad_perm 0xB1 = lane ^ 1, 0x4E = lane ^ 2, row_half_mirror 0x141 = 7 - lane within
@@ -584,17 +584,18 @@ __device__ inline uint32_t hash32(uint32_t x) {
 
 // One thread per eigenvalue alone makes both halves chains that most of a workgroup waits for.
 // Bisection: G lanes per eigenvalue evaluate the brackets of the next 3, 2 or 1 trisection steps
-// at once (16 lanes, the two points of a bracket each, for keep <= 16; 8, a point each, for
-// keep <= 32; 4 for keep <= 64; one past that, where the lanes are busy: eight points per
-// eigenvalue took 5.4 instead of 5.2 ms per 2048 n = 256 matrices); the brackets, their points
-// and the steps taken are those of one step at a time, so the eigenvalues are the same bits.
-// Inverse iteration: the factors and the vector of n keep <= TRI_LDS_MAX elements stay in LDS
-// (LDSF), larger ones are loaded CH steps at a time, one memory latency per CH steps of a solve's
-// chain (8 for keep > 64, whose occupancy 16 costs: 1024 n = 256 matrices 2.32 against 3.10 ms).
+// at once (16 lanes, the two points of a bracket each; 8, a point each; 4 two steps; 1 one); the
+// brackets, their points and the steps taken are those of one step at a time, so the eigenvalues
+// are the same bits.  Past 64 kept the lanes are busy with one each (eight points per eigenvalue
+// took 5.4 instead of 5.2 ms per 2048 n = 256 matrices).
+// Inverse iteration: the factors and the vector of n keep elements stay in LDS (LDSF) or are
+// loaded CH steps at a time, one memory latency per CH steps of a solve's chain.  heev_phase
+// chooses G, LDSF and CH by keep and by how full the batch makes the chip.
 // Per launch, one lane per eigenvalue with factors in memory 4 steps at a time -> this: 15
-// matrices of n = 32 143 -> 65 us, n = 64 260 -> 107, n = 128 421 -> 248; 500 of n = 100 541 ->
-// 424, 512 of n = 128 514 -> 376, 1024 of n = 256 2.57 -> 2.32 ms.  What is left is the chain of
-// the Sturm counts (55% at n = 64), then the factorisation's divisions.
+// matrices of n = 32 143 -> 63 us, n = 64 260 -> 108, n = 128 421 -> 246; 512 of n = 100 398 ->
+// 290, of n = 128 497 -> 363; 2048 of n = 64 624 -> 383, of n = 128 1371 -> 989; 1024 of n = 256
+// 2.59 -> 2.35 ms.  What is left is the chain of the Sturm counts (55% at n = 64), then the
+// factorisation's divisions.
 template <bool LDSF, int CH>
 __global__ __launch_bounds__(ET) void k_tri_eig(int n, int keep, int G, double zero_tol, double* __restrict__ ws, long long sW,
                                                 double* __restrict__ evals, long long sE, double* __restrict__ kept_sum,
@@ -1581,10 +1582,19 @@ hipError_t heev_phase(int phase, int n, int keep, double zero_tol, void* A, long
       break;
     case 1:
     {
-      const int G = keep <= 16 ? 16 : keep <= 32 ? 8 : keep <= 64 ? 4 : 1;
-      if ((long long)n * keep <= TRI_LDS_MAX)
+      // Lanes per eigenvalue and the factors' place, by how full the chip is: with a workgroup per CU
+      // (256) LDS and lanes lie idle otherwise, with two or three each may still have its share of
+      // the LDS, and past that the workgroups hide each other's chains, which LDS that limits their
+      // number and points evaluated ahead only cost.  Matrices of n = 64, keep 32: 256 in LDS 111 us,
+      // in memory 125; 257 203 and 139; 2048 836 and 383.  n = 34, keep 17: 512 78 and 86, 2048 283
+      // and 220.  keep 16, 16 or 8 lanes: 256 of n = 128 193 and 197 us, 2048 of n = 64 416 and 349.
+      // Chunks of 16 or 8 steps: 512 of n = 256 1.68 and 1.74 ms, 1024 3.15 and 2.35.  The bits are
+      // the same for every choice.
+      const int G = keep <= (batch <= 256 ? 16 : 8) ? 16 : keep <= 32 ? 8 : keep <= 64 ? 4 : 1;
+      const int lds_max = batch <= 256 ? TRI_LDS_MAX : batch <= 512 ? TRI_LDS_MAX / 2 : batch <= 768 ? TRI_LDS_MAX / 4 : 0;
+      if (n * keep <= lds_max)
         hipLaunchKernelGGL((k_tri_eig<true, 8>), dim3(batch), dim3(ET), sizeof(double) * 6 * n * keep, st, n, keep, G, zero_tol, ws, sW, evals, sE, kept_sum, active);
-      else if (keep <= 64)
+      else if (batch <= 512)
         hipLaunchKernelGGL((k_tri_eig<false, 16>), dim3(batch), dim3(ET), 0, st, n, keep, G, zero_tol, ws, sW, evals, sE, kept_sum, active);
       else
         hipLaunchKernelGGL((k_tri_eig<false, 8>), dim3(batch), dim3(ET), 0, st, n, keep, G, zero_tol, ws, sW, evals, sE, kept_sum, active);

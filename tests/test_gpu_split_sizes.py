@@ -48,3 +48,31 @@ def test_two_block_hops(chi, n, depth):
         assert np.abs(disc - np.array(eps)).max() < 1e-10
         truncated += int((np.array(eps) > 1e-9).sum())
     assert truncated > 0
+
+
+@pytest.mark.parametrize("chi,n", [(4, 10), (8, 10), (10, 10), (16, 10), (24, 10), (40, 12)])
+def test_results_do_not_depend_on_the_batch_size(chi, n):
+    """The eigenpair kernel's lanes per eigenvalue, chunks and LDS use follow the batch size (lines
+    at 256, 512 and 768): every matrix is solved by the same operations in the same order, so the
+    first trajectories of any batch agree to the bit."""
+    import torch
+
+    from paper_2508_05745_amd import mpsb as M
+    depth = 8
+    c = I.brickwork(n, depth, seed=800 + chi, channel=I.dephasing(0.1))
+    ref = None
+    for n_traj in (12, 257, 513, 769):
+        b = M.Batch(n_traj, n, chi, M.FP64, 17)
+        b.set_autotune(False)      # (the theta tile is tuned for batches of 64 on)
+        b.set_circuit(c, M.ORTHOGONAL)
+        d = torch.zeros((n_traj, n // 2), dtype=torch.float64, device="cuda")
+        got = []
+        for l in range(depth):
+            b.apply_layer(l, discarded=d)
+            got.append(d[:12].clone())
+        got.append(b.expect()[2][:12].clone())
+        b.sync()
+        b.close()
+        ref = ref or got
+        assert all(torch.equal(x, y) for x, y in zip(ref, got)), (chi, n_traj)
+    assert max(x.max().item() for x in ref[:depth]) > 1e-9

@@ -55,14 +55,15 @@ __device__ inline void inv_sum(const c64d (&x)[16], double (&re)[2], double (&im
   }
 }
 template <int JJ>
-__device__ inline void inv_cols(c64d (&x)[16], int ii, const double* ipiv) {
+__device__ inline void inv_cols(c64d (&x)[16], int ii, int nc, const double* ipiv) {   // columns JJ .. nc - 1
   if constexpr (JJ < 16) {
+    if (JJ >= nc) return;
     const double dj = ipiv[JJ];
     double re[2] = {0, 0}, im[2] = {0, 0};
     inv_sum<JJ, 0>(x, re, im);
     if (ii < JJ) x[JJ] = c64d{-dj * (re[0] + re[1]), -dj * (im[0] + im[1])};
     if (ii == JJ) x[JJ] = c64d{dj, 0.0};
-    inv_cols<JJ + 1>(x, ii, ipiv);
+    inv_cols<JJ + 1>(x, ii, nc, ipiv);
   }
 }
 
@@ -73,11 +74,12 @@ __device__ inline void inv_cols(c64d (&x)[16], int ii, const double* ipiv) {
 // waves apply the previous panel's update to the rows past it; the instances for smaller n leave
 // room for several workgroups per CU.  Every element's operations and their order are those of
 // the column-by-column form (two barriers per column, one instance for all n), bit for bit.
-// Per launch (FP64, 2 n rows), that form -> this one: 1000 trajectories of n = 16 120 -> 28 us,
-// n = 32 222 -> 62; 512 of n = 64 235 -> 122, n = 100 538 -> 431; 1024 of n = 128 1465 -> 1129;
-// 15 of n = 32 58 -> 39, n = 64 118 -> 84, n = 128 334 -> 254.  At n = 128 a workgroup spends a
-// third of that in the product with R^-1 (two thirds of its matrix-core time), a quarter in the
-// panels and a fifth in the inverse's block columns.
+// Per launch (FP64, 2 n rows), that form -> this one: 15 trajectories of n = 1 7.1 -> 5.2 us, n = 4
+// 9.8 -> 6.4 (the ends of every chain; 11.4 and 11.8 with every column of a panel and of a diagonal
+// block worked through), n = 32 58 -> 37, n = 64 116 -> 79, n = 128 333 -> 252; 512 of n = 64
+// 231 -> 117, n = 100 529 -> 419; 2048 of n = 16 234 -> 51, n = 32 435 -> 116, n = 128 2905 -> 2230.
+// At n = 128 a workgroup spends a third of that in the product with R^-1 (two thirds of its
+// matrix-core time), a quarter in the panels and a fifth in the inverse's block columns.
 // Registers: 128 up to 64 columns, for four workgroups per CU (160 without the spills: 15 of
 // n = 64 84 -> 79 us, but 1024 of n = 40 97 -> 116); 224 at 96, where LDS leaves room for two
 // (against 128 with 0.5 KB of scratch: 15 of n = 96 238 -> 156 us, 500 459 -> 345, 2048 1800 -> 1404).
@@ -123,6 +125,7 @@ __global__ __launch_bounds__(HT, NMAX > 64 ? 2 : 4) void k_hop_chol(int n, int l
     const bool up = KS > 1 && c0 >= 64;    // the panel's own columns are in the second set
 #pragma unroll
     for (int a = 0; a < CB; ++a) {
+      if (NMAX <= 64 && c0 + a >= n) break;   // (n < 8 mostly: at 65 columns and more the test costs 2%)
       const c64d own = up ? v[a][KS - 1] : v[a][0];
       const double p = lane_f64(own.re, l0 + a);
       const bool keep = p > cut && p > 0.0;
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(HT, NMAX > 64 ? 2 : 4) void k_hop_chol(int n, int l
     c64d x[16];
 #pragma unroll
     for (int l = 0; l < 16; ++l) x[l] = (l >= ii && l < bs) ? R[pk(r0 + ii, r0 + l, n)] : c64d{0, 0};
-    inv_cols<0>(x, ii, ipiv + min(r0, NMAX - 16));
+    inv_cols<0>(x, ii, NMAX <= 64 ? min(n, 16) : 16, ipiv + min(r0, NMAX - 16));
 #pragma unroll
     for (int l = 0; l < 16; ++l)
       if (l >= ii && l < bs) R[pk(r0 + ii, r0 + l, n)] = x[l];

@@ -1332,10 +1332,10 @@ __global__ __launch_bounds__(BTS_NT) void k_bt_small(int n, int keep, const c64d
 // numbered so that they run on one XCD); the panel is written out once.
 // MFMA lane layout (f64 16x16x4): A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
 // D[i][j] in lane j + 16 (i % 4), register i / 4.
-// E3a: parts workgroups per matrix, each every parts-th block; a row of T per lane, in registers.
-// A block is a chain (S, then 120 products); one workgroup per matrix for all blocks left the chip
-// idle below about 1024 matrices.  E3a + E3b, matrix n x batch: 256 x 15 290 -> 114 us, 256 x 256
-// 822 -> 685, 512 x 192 4.70 -> 4.32 ms; 256 x 1024 (one part) 2.59 -> 2.63 ms.
+// E3a for few matrices: parts workgroups per matrix, each every parts-th block, the rows of a block
+// over the four waves; a row of T per lane, in registers.  A block is a chain (S, then 120
+// products), and one workgroup per matrix for all blocks left the chip idle.  E3a + E3b: 256 x 15
+// (matrix n x batch, keep n / 2) 294 -> 112 us, 192 x 60 238 -> 116.
 __global__ __launch_bounds__(256) void k_bt_tfac(int n, const c64d* __restrict__ Ag, long long sA, double* __restrict__ ws,
                                                  long long sW, int keep, int parts, const int* __restrict__ active) {
   const int mat = blockIdx.x / parts, part = blockIdx.x - mat * parts;
@@ -1379,6 +1379,63 @@ __global__ __launch_bounds__(256) void k_bt_tfac(int n, const c64d* __restrict__
       for (int b = 0; b < 16; ++b) Tg[(long long)blk * 256 + tid * 16 + b] = T[b];
     }
     // (the next block writes Sv two barriers from here, after this wave has read it)
+  }
+}
+
+// LDS written by a wave is read by the same wave: no workgroup barrier
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// E3a for many matrices: a wave per block, no barriers.  The four partial sums of S (rows of equal
+// i / 4 mod 4 below the block's first) stay in the wave's accumulators and are added in the order
+// of the other form, so T has its bits.  Three waves of four waited there while one made T.
+// E3a + E3b, one workgroup per matrix for all blocks -> the other form -> this: 256 x 1024 2.58 ->
+// 2.63 -> 2.50 ms, 256 x 2048 5.15 -> 5.23 -> 4.96, 512 x 512 11.57 -> 11.42 -> 11.23 (all blocks
+// of 256 x 2048 in waves of their own 5.11).
+__global__ __launch_bounds__(256) void k_bt_tfac_wave(int n, const c64d* __restrict__ Ag, long long sA, double* __restrict__ ws,
+                                                      long long sW, int keep, int parts, const int* __restrict__ active) {
+  const int mat = blockIdx.x / parts, part = blockIdx.x - mat * parts;
+  if (active && !active[mat]) return;
+  __shared__ c64d Sw[4][16][16];
+  const c64d* A = Ag + mat * sA;
+  c64d* Tg = (c64d*)(ws + mat * sW + bt_tfac_offset(n, keep));
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r16 = lane & 15, kq = lane >> 4;
+  const int nblk = (n - 2 + 15) / 16;
+  c64d(*Sv)[16] = Sw[wv];
+  for (int blk = 4 * part + wv; blk < nblk; blk += 4 * parts) {
+    const int j0 = 16 * blk, nb = min(16, n - 2 - j0);
+    v4d_t sr[4], si[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) sr[w] = si[w] = v4d_t{0, 0, 0, 0};
+    for (int i0 = j0 + 1; i0 < n; i0 += 16) {
+      c64d v[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int row = i0 + 4 * w + kq;
+        v[w] = (row < n && r16 < nb && row > j0 + r16) ? A[(long long)row * n + j0 + r16] : c64d{0, 0};
+      }
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        sr[w] = mfma64(v[w].re, v[w].re, sr[w]);
+        sr[w] = mfma64(v[w].im, v[w].im, sr[w]);
+        si[w] = mfma64(v[w].re, v[w].im, si[w]);
+        si[w] = mfma64(-v[w].im, v[w].re, si[w]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      Sv[kq + 4 * r][r16] = c64d{sr[0][r] + sr[1][r] + sr[2][r] + sr[3][r], si[0][r] + si[1][r] + si[2][r] + si[3][r]};
+    wave_sync();
+    if (lane < 16) {
+      c64d T[16];
+      bt_trow(Sv, lane, nb, T);
+#pragma unroll
+      for (int b = 0; b < 16; ++b) Tg[(long long)blk * 256 + lane * 16 + b] = T[b];
+    }
+    wave_sync();   // S is free for the wave's next block
   }
 }
 
@@ -1622,9 +1679,16 @@ hipError_t heev_phase(int phase, int n, int keep, double zero_tol, void* A, long
         break;
       }
       // 128 < n <= 512: MFMA panel form (T factors, then 16-column panels)
-      // about 1024 workgroups for the T factors
+      // T factors by about 1024 workgroups, from about 100 matrices on a block per wave (matrix n x
+      // batch, a block per workgroup and per wave: 256 x 15 112 and 125 us, 130 x 64 70 and 74; 130 x
+      // 100 79 and 77, 256 x 128 329 and 317)
       const int nblk = (n - 2 + 15) / 16, parts = batch >= 1024 ? 1 : min(nblk, 1024 / batch);
-      hipLaunchKernelGGL(k_bt_tfac, dim3(parts * batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, parts, active);
+      if (batch < 96) {
+        hipLaunchKernelGGL(k_bt_tfac, dim3(parts * batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, parts, active);
+      } else {
+        const int pw = min((nblk + 3) / 4, parts);
+        hipLaunchKernelGGL(k_bt_tfac_wave, dim3(pw * batch), dim3(256), 0, st, n, (const c64d*)A, sA, ws, sW, keep, pw, active);
+      }
       if (n <= 256)
         hipLaunchKernelGGL((k_bt_panel<256, 512>), dim3((unsigned)blocks), dim3(512), 0, st, n, keep, (const c64d*)A, sA, ws, sW, (c64d*)Z, sZ, np, active);
       else

@@ -50,18 +50,19 @@ def test_two_block_hops(chi, n, depth):
     assert truncated > 0
 
 
-@pytest.mark.parametrize("chi,n", [(4, 10), (8, 10), (10, 10), (16, 10), (24, 10), (40, 12)])
-def test_results_do_not_depend_on_the_batch_size(chi, n):
+@pytest.mark.parametrize("chi,n,batches", [(c, n, (12, 257, 513, 769)) for c, n in [(4, 10), (8, 10), (10, 10), (16, 10), (24, 10), (40, 12)]]
+                         + [(66, 14, (12, 95, 96)), (130, 16, (12, 96))])
+def test_results_do_not_depend_on_the_batch_size(chi, n, batches):
     """The eigenpair kernel's lanes per eigenvalue, chunks and LDS use follow the batch size (lines
-    at 256, 512 and 768): every matrix is solved by the same operations in the same order, so the
+    at 256, 512 and 768), and so does the form of the T factors above 128 rows (96): every matrix is solved by the same operations in the same order, so the
     first trajectories of any batch agree to the bit."""
     import torch
 
     from paper_2508_05745_amd import mpsb as M
-    depth = 8
+    depth = 8 if n < 16 else 10
     c = I.brickwork(n, depth, seed=800 + chi, channel=I.dephasing(0.1))
     ref = None
-    for n_traj in (12, 257, 513, 769):
+    for n_traj in batches:
         b = M.Batch(n_traj, n, chi, M.FP64, 17)
         b.set_autotune(False)      # (the theta tile is tuned for batches of 64 on)
         b.set_circuit(c, M.ORTHOGONAL)

@@ -81,8 +81,10 @@ __device__ inline void inv_cols(c64d (&x)[16], int ii, int nc, const double* ipi
 // At n = 128 a workgroup spends a third of that in the product with R^-1 (two thirds of its
 // matrix-core time), a quarter in the panels and a fifth in the inverse's block columns.
 // Registers: 128 up to 64 columns, for four workgroups per CU (160 without the spills: 15 of
-// n = 64 84 -> 79 us, but 1024 of n = 40 97 -> 116); 224 at 96, where LDS leaves room for two
-// (against 128 with 0.5 KB of scratch: 15 of n = 96 238 -> 156 us, 500 459 -> 345, 2048 1800 -> 1404).
+// n = 64 84 -> 79 us, but 1024 of n = 40 97 -> 116); 224 at 96, whose eight waves then fill a CU
+// alone although its LDS would admit two workgroups (at 128 registers and 0.5 KB of scratch -> 224,
+// FP32 / FP64: 15 of n = 96 258 / 237 -> 158 / 153 us, 2048 1754 / 1798 -> 1361 / 1405; only FP32 of
+// 65 to 80 columns gains by the second workgroup, 512 of n = 72 223 against 233).
 template <typename T, int NMAX, int HT>
 __global__ __launch_bounds__(HT, NMAX > 64 ? 2 : 4) void k_hop_chol(int n, int left_to_right, int other, const c64d* __restrict__ Eg,
                                                  long long sE, cplx<T>* __restrict__ C, long long sC,
@@ -417,8 +419,9 @@ void launch_chol(int n, int left_to_right, int other, const void* E, long long s
 template <typename T>
 void launch_chol_n(int n, int left_to_right, int other, const void* E, long long sE, void* C, long long sC, void* Rout,
                    long long sR, double tol, int n_traj, hipStream_t st) {
-  // the smallest triangle that holds the factor: 9, 35 and 78 KB of LDS leave room for several
-  // workgroups per CU, the 136 KB of the last for one (at n <= 64 with that one: 222, 235 us)
+  // the smallest triangle that holds the factor: 9 and 35 KB of LDS leave room for several workgroups
+  // per CU (1000 of n = 32 and 512 of n = 64 with the last one: 222, 235 us against 62, 117); the
+  // 78 KB instance runs one by its registers, the 136 KB one by its LDS
   if (n <= 32) launch_chol<T, 32, 256>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
   else if (n <= 64) launch_chol<T, 64, 256>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);
   else if (n <= 96) launch_chol<T, 96, 512>(n, left_to_right, other, E, sE, C, sC, Rout, sR, tol, n_traj, st);

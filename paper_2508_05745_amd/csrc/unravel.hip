@@ -508,7 +508,6 @@ __device__ __attribute__((noinline)) void optimal_mixing(const cd (&rho)[2][2], 
       out.W[i][j] = i < r ? acc : cz();
     }
   out.conc = conc;
-  out.separable = cdiff > 0.0 ? 0 : 1;
 }
 
 // The events' complex products with the fused operations written out: left to the compiler their

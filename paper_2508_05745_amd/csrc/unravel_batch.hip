@@ -4,9 +4,13 @@
 // trajectory's events keep the other form: a sweep carries their branch operators through every
 // later truncation, and discarded weights at rounding level follow their last place (up to 1e-3
 // of such a weight over four layers, against 2 % of a chi-64 layer).
+// The steps between stand in both files: shared as templates over the two arithmetics, the compiler's
+// fused operations in the events, and with them every recorded run's last place, were others, and the
+// events slower (2048 single-site events 7.9 -> 10.6 us without, 128 -> 134 with the eigensolver).
+// So what is mended in one belongs into the other.
 // Bound by the serial chain of the Jacobi sweeps (1000 items are 16 waves on the chip; 200000 are
 // three waves per SIMD).  Against the real 8 x 8 embedding with library divisions and 576 bytes of
-// per-lane scratch: 1000 items 137 -> 72 us, 200000 items 596 -> 295 us.
+// per-lane scratch: 1000 items 137 -> 72 us, 200000 items 596 -> 292 us.
 #include <float.h>
 
 #include "common.h"
@@ -606,7 +610,6 @@ __device__ void optimal_mixing(const cd (&rho)[2][2], const cd (&K)[4][2][2], in
       out.W[i][j] = i < r ? acc : cz();
     }
   out.conc = conc;
-  out.separable = cdiff > 0.0 ? 0 : 1;
 }
 
 __device__ void mixed_ops(const cd (&K)[4][2][2], int r, const cd (&W)[4][4], const cd (&rho)[2][2],

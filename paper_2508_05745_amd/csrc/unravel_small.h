@@ -21,9 +21,7 @@ __device__ inline cd yy_flip(const cd (&v)[4], int i) {
 
 struct UnravelOut {
   cd W[4][4];     // [i][j], i < r: K'_j = sum_i W[i][j] K_i
-  double p[4];
   double conc;
-  int separable;
 };
 
 }  // namespace mpsb
